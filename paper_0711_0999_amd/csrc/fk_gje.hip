@@ -32,6 +32,7 @@
 // Rows are never swapped: with r = piv and rinv = rowcol the inverse is
 // inv(A)[a][b] = X[r[a]][rinv[b]], which the reduction kernels read directly.
 #include "fk_internal.h"
+#include "fk_tile.h"
 
 #include <float.h>
 #include <limits.h>
@@ -39,26 +40,6 @@
 #include <atomic>
 
 namespace fk {
-
-// 16x16x4 matrix-core products.  Operands: lane l holds A[l%16][l/16] and
-// B[l/16][l%16].  The accumulator layout differs between the two precisions
-// (measured on gfx950): register v of lane l holds D[row][l%16] with
-//   f64: row = (l/16) + 4 v      f32: row = 4 (l/16) + v.
-template <typename T> struct Mfma;
-template <> struct Mfma<double> {
-  typedef double v4 __attribute__((ext_vector_type(4)));
-  __device__ static inline v4 run(double a, double b, v4 c) {
-    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
-  }
-  __device__ static inline int drow(int lk, int v) { return lk + 4 * v; }
-};
-template <> struct Mfma<float> {
-  typedef float v4 __attribute__((ext_vector_type(4)));
-  __device__ static inline v4 run(float a, float b, v4 c) {
-    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-  }
-  __device__ static inline int drow(int lk, int v) { return 4 * lk + v; }
-};
 
 template <typename T> __device__ inline T big_value();
 template <> __device__ inline double big_value<double>() { return DBL_MAX; }
@@ -714,43 +695,19 @@ __global__ __launch_bounds__(512, 1) void k_fix(
 // ------------------------------------------------------------------ update
 // C <- mask_P(C) + M B for the listed tiles of (32 WR) x 64: 2 WR waves as
 // WR x 2 blocks of 32 x 32 (WR = 2: 64 x 64 tiles, two workgroups per CU;
-// WR = 4: 128 x 64 tiles sharing each B chunk, one workgroup per CU).  K in
-// chunks of kKC, double-buffered through LDS with the next chunk's global
-// loads in flight during the current chunk's MFMAs; within a chunk the next
-// k-step's operands are read from LDS before the current k-step's MFMAs.
-// Interior tiles (whole rows, columns and K chunks) skip every clamp and
-// mask.  Each complex product takes three real ones (Gauss): P1 = Re a Re b,
-// P2 = Im a Im b and P3 = (Re a + Im a)(Re b + Im b) accumulate separately,
-// and the epilogue forms Re = P1 - P2, Im = P3 - P1 - P2: a quarter fewer
-// MFMAs than the four-product form, with a normwise (not componentwise) error
-// bound of the same order.  The C tile is read in the epilogue.
+// WR = 4: 128 x 64 tiles sharing each B chunk, one workgroup per CU).
+// Edge tiles load clamped rows and columns and do not store what lies outside.
 template <typename T, int WR>
 __global__ __launch_bounds__(128 * WR, 4 / WR) void k_update(
     cplx<T>* __restrict__ xbuf, const cplx<T>* __restrict__ bbuf,
     const int* __restrict__ rowcolbuf, const MatDesc* __restrict__ descs,
     const TileItem* __restrict__ items, int nitems) {
-  typedef typename Mfma<T>::v4 v4;
-  constexpr int TR = 32 * WR, NT = 128 * WR;
-  constexpr int AP = kKC + 1, BP = kTile + 1;
-  __shared__ cplx<T> As[2][TR * AP];
-  __shared__ cplx<T> Bsh[2][kKC * BP];
-  constexpr int kLA = TR * kKC / NT;      // chunk loads per thread
-  constexpr int kLB = kKC * kTile / NT;
-  static_assert(NT % kKC == 0 && NT % kTile == 0, "load map");
-
-  const int tid = threadIdx.x;
-  const int lane = tid & 63, wave = tid >> 6;
-  const int wr = wave >> 1, wc = wave & 1;
-  const int li = lane & 15, lk = lane >> 4;
+  typedef TileProduct<T, WR> P;
+  __shared__ typename P::Lds lds;
   const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
   const int per = gridDim.x >> 3;
   const int chunk = (nitems + 7) >> 3;
   const int lo = xcd * chunk, hi = min(nitems, lo + chunk);
-  // this thread's chunk loads: A rows ai0 + t (NT / kKC) at column ak of the
-  // chunk, B rows bk0 + t (NT / kTile) at column bc of the tile
-  const int ak = tid % kKC, ai0 = tid / kKC;
-  const int bc = tid % kTile, bk0 = tid / kTile;
-  constexpr int AST = NT / kKC, BST = NT / kTile;
 
   for (int it = lo + slot; it < hi; it += per) {
     const TileItem ti = items[it];
@@ -758,176 +715,30 @@ __global__ __launch_bounds__(128 * WR, 4 / WR) void k_update(
     const int n = d.n, ld = d.ld;
     // M = columns [J0, J0 + wO), B = side-buffer rows [b0, b0 + wO)
     const int J0 = ti.jb * kNBO, wO = ti.kw;
-    const int nch = (wO + kKC - 1) / kKC;
-    const int r0 = ti.tr * TR, c0 = ti.tc * kTile;
+    const int r0 = ti.tr * P::TR, c0 = ti.tc * kTile;
     cplx<T>* xm = xbuf + d.xoff;
-    const cplx<T>* bm = bbuf + d.boff + (size_t)ti.b0 * ld;
     const int* rowcol = rowcolbuf + d.ioff;
-    const bool full = r0 + TR <= n && c0 + kTile <= n && (wO % kKC) == 0;
-    const cplx<T>* arow[kLA];
-#pragma unroll
-    for (int t = 0; t < kLA; ++t)
-      arow[t] = xm + (size_t)min(r0 + ai0 + AST * t, n - 1) * ld + J0;
-    const cplx<T>* bcol = bm + min(c0 + bc, n - 1);
-    cplx<T> pa[kLA], pb[kLB];
-    auto gload = [&](int kb) {
-      if (full) {
-#pragma unroll
-        for (int t = 0; t < kLA; ++t) pa[t] = arow[t][kb + ak];
-#pragma unroll
-        for (int t = 0; t < kLB; ++t) pb[t] = bcol[(size_t)(kb + bk0 + BST * t) * ld];
-      } else {
-#pragma unroll
-        for (int t = 0; t < kLA; ++t) pa[t] = arow[t][min(kb + ak, wO - 1)];
-#pragma unroll
-        for (int t = 0; t < kLB; ++t)
-          pb[t] = bcol[(size_t)min(kb + bk0 + BST * t, wO - 1) * ld];
-      }
-    };
-    auto lstore = [&](int kb, int buf) {
-      if (!full) {
-#pragma unroll
-        for (int t = 0; t < kLA; ++t)
-          if (!(r0 + ai0 + AST * t < n && kb + ak < wO)) pa[t].re = pa[t].im = T(0);
-#pragma unroll
-        for (int t = 0; t < kLB; ++t)
-          if (!(kb + bk0 + BST * t < wO && c0 + bc < n)) pb[t].re = pb[t].im = T(0);
-      }
-#pragma unroll
-      for (int t = 0; t < kLA; ++t) As[buf][(ai0 + AST * t) * AP + ak] = pa[t];
-#pragma unroll
-      for (int t = 0; t < kLB; ++t) Bsh[buf][(bk0 + BST * t) * BP + bc] = pb[t];
-    };
-
-    // Edge tiles with at most 16 valid rows (or columns) use a strip layout:
-    // wave w multiplies the single 16 x 16 block at columns (rows) 16 w of
-    // the strip, a quarter of an interior tile's matrix-core work, instead of
-    // a 32 x 32 quarter that lies mostly outside the matrix.  The choice is
-    // the same for the whole workgroup.
-    const int edge = (n - r0 <= 16) ? 1 : ((n - c0 <= 16) ? 2 : 0);
-    const int er0 = edge == 2 ? 16 * wave : 0;   // strip block origin (rows)
-    const int ec0 = edge == 1 ? 16 * wave : 0;   // strip block origin (columns)
-    // waves whose strip block lies inside the tile (all of them for a
-    // 64 x 64 tile; the first four of a 128-row tile's eight in a row strip)
-    const bool eact = edge == 1 ? ec0 < kTile : er0 < TR;
-    // pivot-row mask of the rows this lane writes
+    P tp;
+    tp.begin(lds, xm + J0, ld, r0, n, bbuf + d.boff + (size_t)ti.b0 * ld, ld, c0, n, wO);
+    // pivot columns of the rows this lane writes
     int rcv[2][4];
 #pragma unroll
     for (int ii = 0; ii < 2; ++ii)
 #pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const int rr = edge ? er0 + 16 * ii : 32 * wr + 16 * ii;
-        rcv[ii][v] = rowcol[min(r0 + rr + Mfma<T>::drow(lk, v), n - 1)];
-      }
-    v4 p1[2][2], p2[2][2], p3[2][2];
-#pragma unroll
-    for (int ii = 0; ii < 2; ++ii)
-#pragma unroll
-      for (int jj = 0; jj < 2; ++jj)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          p1[ii][jj][v] = T(0);
-          p2[ii][jj][v] = T(0);
-          p3[ii][jj][v] = T(0);
-        }
-    gload(0);
-    lstore(0, 0);
-    __syncthreads();
-
-    // the MFMAs of one K chunk from LDS buffer buf; operands of the next
-    // k-step are read before the current k-step's products (ping-pong)
-    auto mfma_chunk = [&](int buf) {
-      const cplx<T>* as = As[buf];
-      const cplx<T>* bs = Bsh[buf];
-      cplx<T> a[2][2], b[2][2];
-#pragma unroll
-      for (int ii = 0; ii < 2; ++ii) a[0][ii] = as[(32 * wr + 16 * ii + li) * AP + lk];
-#pragma unroll
-      for (int jj = 0; jj < 2; ++jj) b[0][jj] = bs[lk * BP + 32 * wc + 16 * jj + li];
-#pragma unroll
-      for (int s = 0; s < kKC / 4; ++s) {
-        const int cur = s & 1;
-        if (s + 1 < kKC / 4) {
-          const int k = 4 * (s + 1);
-#pragma unroll
-          for (int ii = 0; ii < 2; ++ii)
-            a[cur ^ 1][ii] = as[(32 * wr + 16 * ii + li) * AP + k + lk];
-#pragma unroll
-          for (int jj = 0; jj < 2; ++jj)
-            b[cur ^ 1][jj] = bs[(k + lk) * BP + 32 * wc + 16 * jj + li];
-        }
-        T as_[2], bs_[2];
-#pragma unroll
-        for (int ii = 0; ii < 2; ++ii) as_[ii] = a[cur][ii].re + a[cur][ii].im;
-#pragma unroll
-        for (int jj = 0; jj < 2; ++jj) bs_[jj] = b[cur][jj].re + b[cur][jj].im;
-#pragma unroll
-        for (int ii = 0; ii < 2; ++ii)
-#pragma unroll
-          for (int jj = 0; jj < 2; ++jj) {
-            p1[ii][jj] = Mfma<T>::run(a[cur][ii].re, b[cur][jj].re, p1[ii][jj]);
-            p2[ii][jj] = Mfma<T>::run(a[cur][ii].im, b[cur][jj].im, p2[ii][jj]);
-            p3[ii][jj] = Mfma<T>::run(as_[ii], bs_[jj], p3[ii][jj]);
-          }
-      }
-    };
-
-    // strip layout: one 16 x 16 block per wave, accumulated in p*[0][0]
-    auto mfma_chunk_edge = [&](int buf) {
-      if (!eact) return;
-      const cplx<T>* as = As[buf];
-      const cplx<T>* bs = Bsh[buf];
-#pragma unroll
-      for (int s = 0; s < kKC / 4; ++s) {
-        const int k = 4 * s;
-        const cplx<T> a = as[(er0 + li) * AP + k + lk];
-        const cplx<T> b = bs[(k + lk) * BP + ec0 + li];
-        p1[0][0] = Mfma<T>::run(a.re, b.re, p1[0][0]);
-        p2[0][0] = Mfma<T>::run(a.im, b.im, p2[0][0]);
-        p3[0][0] = Mfma<T>::run(a.re + a.im, b.re + b.im, p3[0][0]);
-      }
-    };
-
-    if (!edge) {
-      for (int kc = 0; kc + 1 < nch; ++kc) {
-        const int buf = kc & 1;
-        gload((kc + 1) * kKC);
-        mfma_chunk(buf);
-        lstore((kc + 1) * kKC, buf ^ 1);
-        __syncthreads();
-      }
-      mfma_chunk((nch - 1) & 1);
-    } else {
-      for (int kc = 0; kc + 1 < nch; ++kc) {
-        const int buf = kc & 1;
-        gload((kc + 1) * kKC);
-        mfma_chunk_edge(buf);
-        lstore((kc + 1) * kKC, buf ^ 1);
-        __syncthreads();
-      }
-      mfma_chunk_edge((nch - 1) & 1);
-    }
-    __syncthreads();   // LDS free for this workgroup's next item
-#pragma unroll
-    for (int ii = 0; ii < 2; ++ii)
-#pragma unroll
-      for (int jj = 0; jj < 2; ++jj)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          if (edge && (ii || jj || !eact)) continue;
-          const int row = r0 + (edge ? er0 : 32 * wr + 16 * ii) + Mfma<T>::drow(lk, v);
-          const int col = c0 + (edge ? ec0 : 32 * wc + 16 * jj) + li;
-          if (row < n && col < n) {
-            const int rc = rcv[ii][v];
-            const bool keep = !(rc >= J0 && rc < J0 + wO);
-            const cplx<T> cv = xm[(size_t)row * ld + col];
-            cplx<T> c;
-            const T q1 = p1[ii][jj][v], q2 = p2[ii][jj][v];
-            c.re = (q1 - q2) + (keep ? cv.re : T(0));
-            c.im = ((p3[ii][jj][v] - q1) - q2) + (keep ? cv.im : T(0));
-            xm[(size_t)row * ld + col] = c;
-          }
-        }
+      for (int v = 0; v < 4; ++v) rcv[ii][v] = rowcol[min(tp.row(ii, v), n - 1)];
+    tp.run(lds);
+    typename P::c2 cv[2][2][4], *xc = reinterpret_cast<typename P::c2*>(xm);
+    tp.for_each_output([&](int ii, int jj, int v, bool in, unsigned off) {
+      if (in) cv[ii][jj][v] = *at_byte(xc, off);
+    });
+    tp.for_each_output([&](int ii, int jj, int v, bool in, unsigned off) {
+      const bool keep = !(rcv[ii][v] >= J0 && rcv[ii][v] < J0 + wO);
+      typename P::c2 c = tp.value(ii, jj, v);
+      c.x += keep ? cv[ii][jj][v].x : T(0);
+      c.y += keep ? cv[ii][jj][v].y : T(0);
+      if (in) *at_byte(xc, off) = c;
+    });
+    if (per < hi - lo) __syncthreads();   // LDS free for the next item
   }
 }
 

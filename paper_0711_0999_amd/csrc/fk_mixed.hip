@@ -9,10 +9,9 @@
 // correction one more dense GEMM.
 #include "fk_internal.h"
 #include "fk_kernels.h"
+#include "fk_tile.h"
 
 namespace fk {
-
-typedef double v4d __attribute__((ext_vector_type(4)));
 
 // out[m][a][b] = X[m][piv_m[a]][rowcol_m[b]] in FP64 (undo the logical pivoting)
 template <typename TI>
@@ -32,123 +31,35 @@ __global__ void k_unpermute(const cplx<TI>* __restrict__ x, size_t xstride,
 }
 
 // C[m] = beta Cin[m] + A[m] B[m] for n x n complex128 matrices (leading
-// dimension n).  sA = 0 shares A across the batch.  64 x 64 tiles, 2 x 2 waves
-// of 32 x 32, K in double-buffered chunks of 16, f64 matrix cores, three real
-// products per complex one (Gauss: Re = P1 - P2, Im = P3 - P1 - P2 with
-// P1 = Re a Re b, P2 = Im a Im b, P3 = (Re a + Im a)(Re b + Im b)).
-constexpr int kGT = 64, kGK = 16;
+// dimension n).  sA = 0 shares A across the batch.  One 64 x 64 tile product
+// of the trailing update's form (fk_tile.h) per workgroup.
 __global__ __launch_bounds__(256, 2) void k_bgemm(
     c64* __restrict__ C, const c64* __restrict__ Cin, double beta,
     const c64* __restrict__ A, size_t sA, const c64* __restrict__ B, int n,
     int nmat) {
-  constexpr int AP = kGK + 1, BP = kGT + 1;
-  __shared__ c64 As[2][kGT * AP];
-  __shared__ c64 Bs[2][kGK * BP];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wr = wave >> 1, wc = wave & 1, li = lane & 15, lk = lane >> 4;
-  const int nt = (n + kGT - 1) / kGT;
+  typedef TileProduct<double, 2> P;
+  __shared__ P::Lds lds;
+  const int nt = (n + kTile - 1) / kTile;
   const int per_m = nt * nt;
   const int nitems = per_m * nmat;
-  const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3, per = gridDim.x >> 3;
+  const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
   const int chunk = (nitems + 7) >> 3;
-  const int lo = xcd * chunk, hi = min(nitems, lo + chunk);
+  const int it = xcd * chunk + slot;
+  if (slot >= chunk || it >= nitems) return;
   const size_t ss = (size_t)n * n;
-  const int nch = (n + kGK - 1) / kGK;
-  for (int it = lo + slot; it < hi; it += per) {
-    const int m = it / per_m, t = it - (it / per_m) * per_m;
-    const int tc = t / nt, tr = t - (t / nt) * nt;
-    const int r0 = tr * kGT, c0 = tc * kGT;
-    const c64* am = A + sA * m;
-    const c64* bm = B + ss * m;
-    v4d p1[2][2], p2[2][2], p3[2][2];
-#pragma unroll
-    for (int ii = 0; ii < 2; ++ii)
-#pragma unroll
-      for (int jj = 0; jj < 2; ++jj)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          p1[ii][jj][v] = 0.0;
-          p2[ii][jj][v] = 0.0;
-          p3[ii][jj][v] = 0.0;
-        }
-    c64 pa[4], pb[4];
-    auto load = [&](int kb) {
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int e = tid + q * 256;
-        const int i = e / kGK, k = e % kGK;
-        pa[q] = am[(size_t)min(r0 + i, n - 1) * n + min(kb + k, n - 1)];
-        const int kk = e / kGT, c = e % kGT;
-        pb[q] = bm[(size_t)min(kb + kk, n - 1) * n + min(c0 + c, n - 1)];
-      }
-    };
-    auto stash = [&](int buf, int kb) {
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int e = tid + q * 256;
-        const int i = e / kGK, k = e % kGK;
-        c64 a = pa[q];
-        if (!(r0 + i < n && kb + k < n)) a = c64{0.0, 0.0};
-        As[buf][i * AP + k] = a;
-        const int kk = e / kGT, c = e % kGT;
-        c64 b = pb[q];
-        if (!(kb + kk < n && c0 + c < n)) b = c64{0.0, 0.0};
-        Bs[buf][kk * BP + c] = b;
-      }
-    };
-    load(0);
-    stash(0, 0);
-    __syncthreads();
-    for (int kc = 0; kc < nch; ++kc) {
-      const int buf = kc & 1;
-      const bool more = kc + 1 < nch;
-      if (more) load((kc + 1) * kGK);
-#pragma unroll
-      for (int k = 0; k < kGK; k += 4) {
-        double ar[2], ai[2], as_[2], br[2], bi[2], bs_[2];
-#pragma unroll
-        for (int ii = 0; ii < 2; ++ii) {
-          const c64 a = As[buf][(32 * wr + 16 * ii + li) * AP + k + lk];
-          ar[ii] = a.re;
-          ai[ii] = a.im;
-          as_[ii] = a.re + a.im;
-        }
-#pragma unroll
-        for (int jj = 0; jj < 2; ++jj) {
-          const c64 b = Bs[buf][(k + lk) * BP + 32 * wc + 16 * jj + li];
-          br[jj] = b.re;
-          bi[jj] = b.im;
-          bs_[jj] = b.re + b.im;
-        }
-#pragma unroll
-        for (int ii = 0; ii < 2; ++ii)
-#pragma unroll
-          for (int jj = 0; jj < 2; ++jj) {
-            p1[ii][jj] = __builtin_amdgcn_mfma_f64_16x16x4f64(ar[ii], br[jj], p1[ii][jj], 0, 0, 0);
-            p2[ii][jj] = __builtin_amdgcn_mfma_f64_16x16x4f64(ai[ii], bi[jj], p2[ii][jj], 0, 0, 0);
-            p3[ii][jj] = __builtin_amdgcn_mfma_f64_16x16x4f64(as_[ii], bs_[jj], p3[ii][jj], 0, 0, 0);
-          }
-      }
-      if (more) stash(buf ^ 1, (kc + 1) * kGK);
-      __syncthreads();
-    }
-#pragma unroll
-    for (int ii = 0; ii < 2; ++ii)
-#pragma unroll
-      for (int jj = 0; jj < 2; ++jj)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          const int row = r0 + 32 * wr + 16 * ii + lk + 4 * v;  // f64 layout
-          const int col = c0 + 32 * wc + 16 * jj + li;
-          if (row < n && col < n) {
-            const size_t e = ss * m + (size_t)row * n + col;
-            c64 c{0.0, 0.0};
-            if (beta != 0.0) c = Cin[e];
-            const double q1 = p1[ii][jj][v], q2 = p2[ii][jj][v];
-            C[e] = c64{(q1 - q2) + beta * c.re, ((p3[ii][jj][v] - q1) - q2) + beta * c.im};
-          }
-        }
-  }
+  const int m = it / per_m, t = it - m * per_m;
+  const int tc = t / nt, tr = t - tc * nt;
+  P tp;
+  tp.begin(lds, A + sA * m, n, tr * kTile, n, B + ss * m, n, tc * kTile, n, n);
+  tp.run(lds);
+  P::c2* cm = reinterpret_cast<P::c2*>(C + ss * m);
+  const P::c2* im = reinterpret_cast<const P::c2*>(Cin + ss * m);
+  tp.for_each_output([&](int ii, int jj, int v, bool in, unsigned off) {
+    if (!in) return;
+    P::c2 c = tp.value(ii, jj, v);
+    if (beta != 0.0) c += beta * *at_byte(im, off);
+    *at_byte(cm, off) = c;
+  });
 }
 
 // R = I - T X + P in place of P (P = Sigma_t X), T = i I + sub-diagonal tsub
@@ -201,7 +112,7 @@ hipError_t launch_unpermute(const cplx<TI>* x, size_t xstride, int ld,
 hipError_t launch_bgemm(c64* C, const c64* Cin, double beta, const c64* A,
                         size_t sA, const c64* B, int n, int nmat,
                         hipStream_t st) {
-  const int nt = (n + kGT - 1) / kGT;
+  const int nt = (n + kTile - 1) / kTile;
   const long long items = (long long)nt * nt * nmat;
   const int grid = (int)(8 * ((items + 7) / 8));
   hipLaunchKernelGGL(k_bgemm, dim3(grid), dim3(256), 0, st, C, Cin, beta, A,
