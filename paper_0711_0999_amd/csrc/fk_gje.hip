@@ -7,11 +7,10 @@
 //   panel   (one 512-thread workgroup per matrix) eliminates the block's
 //           four 32-column quarters in turn on the n - J0 rows not pivoted in
 //           earlier blocks.  For each column the pivot is the largest
-//           |re|+|im| among the rows not yet pivoted; kIB columns are
-//           eliminated in registers at a time (one row per thread), the rest
-//           of the quarter receives rank-kIB updates (16 lanes per row), and
-//           the other quarter of the half and then the other half receive
-//           the quarter's (half's) transform on the matrix cores.
+//           |re|+|im| among the rows not yet pivoted; groups of kIB columns
+//           are eliminated in registers, and the rest of the quarter, the
+//           other quarter of the half and then the other half receive the
+//           group's (quarter's, half's) transform on the matrix cores.
 //   gather  copies the pivot rows of the step into a side buffer B (their
 //           values before the step outside the block, the block's inverse
 //           pivot submatrix inside it); B holds the rows of two blocks.
@@ -34,16 +33,7 @@
 #include "fk_internal.h"
 #include "fk_tile.h"
 
-#include <float.h>
-#include <limits.h>
-
-#include <atomic>
-
 namespace fk {
-
-template <typename T> __device__ inline T big_value();
-template <> __device__ inline double big_value<double>() { return DBL_MAX; }
-template <> __device__ inline float big_value<float>() { return FLT_MAX; }
 
 template <typename T>
 __device__ inline cplx<T> cmul(const cplx<T>& a, const cplx<T>& b) {
@@ -52,487 +42,620 @@ __device__ inline cplx<T> cmul(const cplx<T>& a, const cplx<T>& b) {
   r.im = a.re * b.im + a.im * b.re;
   return r;
 }
-template <typename T>
-__device__ inline void cfma(cplx<T>& acc, const cplx<T>& a, const cplx<T>& b) {
-  acc.re += a.re * b.re - a.im * b.im;
-  acc.im += a.re * b.im + a.im * b.re;
-}
 
 constexpr int kPW = kPanelThreads / 64;          // waves of the panel kernel
-// Panel shapes: rows per thread and register block, (4, 8) up to kSmallN
-// rows, (kMaxN / kPanelThreads, 4) beyond (fewer columns per register block
-// keep the larger row count in registers).
-constexpr int kSmallN = 2048;
-constexpr int kRPTs = kSmallN / kPanelThreads, kIBs = kIB;
-constexpr int kRPTl = kMaxN / kPanelThreads, kIBl = 4;
-constexpr int kPitch = kNB + 1;                  // padded LDS row (elements)
-static_assert(kMaxN % kPanelThreads == 0 && kSmallN % kPanelThreads == 0, "kMaxN");
+constexpr int kBP = 33;                          // LDS row of a 32-column block
 static_assert(kNBO == 2 * kNB && kTile == kNB, "block sizes");
 
-// ------------------------------------------------------ panel: cross update
-// C <- mask(C) + M B on the columns [c0, c0 + cw) of one matrix's listed rows,
-// with M the already eliminated columns [j0, j0 + w) and B the values of their
-// pivot rows in [c0, c0 + cw) (read before any write: this workgroup owns the
-// matrix).  KW >= w and CW >= cw are the compile-time widths (32 or 64).  The
-// kPW waves form (kPW / (CW/16)) x (CW/16) blocks of (16 RB) x 16 over each
-// tile of TRW rows (at least 64).
-template <typename T, int KW, int CW>
-__device__ __forceinline__ void cross_update(cplx<T>* __restrict__ x, int ld,
-                             const int* __restrict__ rows, int m,
-                             const int* __restrict__ piv,
-                             const int* __restrict__ rowcol, int j0, int w,
-                             int c0, int cw, unsigned char* smem) {
-  typedef typename Mfma<T>::v4 v4;
-  constexpr int NCB = CW / 16, NRW = kPW / NCB;
-  constexpr int RB = 1;
-  constexpr int TRW = 16 * RB * NRW;
-  static_assert(NCB * NRW == kPW && TRW <= kNB + kTile, "waves");
-  constexpr int KP = KW + 1, CP = CW + 1;
-  cplx<T>* Bs = reinterpret_cast<cplx<T>*>(smem);   // [KW][CP]
-  cplx<T>* Ms = Bs + KW * CP;                        // [TRW][KP]
-  constexpr int kLB = KW * CW / kPanelThreads;      // B elements per thread
-  constexpr int kLM = TRW * KW / kPanelThreads;     // M elements per thread
-  static_assert(kLB * kPanelThreads == KW * CW && kLM * kPanelThreads == TRW * KW, "loads");
-  static_assert(KW * CP + TRW * KP <= (kNB + kTile) * kPitch, "LDS");
-  const int tid = threadIdx.x;
-  {
-    int pr[kLB];
-    cplx<T> bv[kLB];
-#pragma unroll
-    for (int t = 0; t < kLB; ++t) {
-      const int l = (tid + t * kPanelThreads) / CW;
-      pr[t] = piv[j0 + min(l, w - 1)];
-    }
-#pragma unroll
-    for (int t = 0; t < kLB; ++t) {
-      const int c = (tid + t * kPanelThreads) % CW;
-      bv[t] = x[(size_t)pr[t] * ld + c0 + min(c, cw - 1)];
-    }
-#pragma unroll
-    for (int t = 0; t < kLB; ++t) {
-      const int e = tid + t * kPanelThreads;
-      const int l = e / CW, c = e % CW;
-      cplx<T> v = bv[t];
-      if (!(l < w && c < cw)) v.re = v.im = T(0);
-      Bs[l * CP + c] = v;
-    }
+// Pivot key of a candidate z, an int that orders like |re| + |im|: the float's
+// bits, or the double's upper word.  Infinities and NaN order above every
+// number (bad_key).
+__device__ __forceinline__ int pivot_key(const c64& z) {
+  return (int)(__double_as_longlong(fabs(z.re) + fabs(z.im)) >> 32);
+}
+__device__ __forceinline__ int pivot_key(const c32& z) {
+  return __float_as_int(fabsf(z.re) + fabsf(z.im));
+}
+template <typename T> __device__ __forceinline__ constexpr int bad_key() {
+  return sizeof(T) == 8 ? 0x7ff00000 : 0x7f800000;
+}
+// Low bits of a key that carry the candidate's place in the row list (counted
+// down, so that among equal keys the lowest row wins) for lists of up to cap.
+constexpr int place_mask(int cap) {
+  int b = 1;
+  while (b < cap) b *= 2;
+  return b - 1;
+}
+
+// Maxima over lanes through the ALU's DPP paths (an LDS permute per step would
+// cost about 100 cycles of latency in a chain of six).
+template <int CTRL, int ROWS> __device__ __forceinline__ int dpp_max(int x) {
+  return max(x, __builtin_amdgcn_update_dpp(x, x, CTRL, ROWS, 0xf, false));
+}
+__device__ __forceinline__ int max_of_wave(int x) {    // uniform
+  x = dpp_max<0x111, 0xf>(x);
+  x = dpp_max<0x112, 0xf>(x);
+  x = dpp_max<0x114, 0xf>(x);
+  x = dpp_max<0x118, 0xf>(x);          // row_shr 8: lane 15 of each row
+  x = dpp_max<0x142, 0xa>(x);          // row_bcast 15 into rows 1 and 3
+  x = dpp_max<0x143, 0xc>(x);          // row_bcast 31 into rows 2 and 3
+  return __builtin_amdgcn_readlane(x, 63);
+}
+
+// This thread's index, opaque to the optimizer: what a panel step derives from
+// it (lane maps, masks, LDS offsets) is formed where the step begins instead
+// of being kept in registers across the whole panel (about 100 of them).
+__device__ __forceinline__ int fresh_tid() {
+  int t = threadIdx.x;
+  asm volatile("" : "+v"(t));
+  return t;
+}
+
+// Where a panel step's matrix entries live: entry e of the block's row list,
+// column c of the step's frame.
+template <typename T> struct InMemory {          // the matrix, rows by list
+  cplx<T>* x;
+  const unsigned* off;                           // byte offset of each entry's row
+  typedef unsigned Ref;
+  __device__ __forceinline__ Ref ref(int e, int c) const {
+    return off[e] + (unsigned)c * (unsigned)sizeof(cplx<T>);
   }
-  const int lane = tid & 63, wave = tid >> 6;
-  const int wr = wave / NCB, wc = wave % NCB;
+  __device__ __forceinline__ cplx<T>* at(Ref r) const { return at_byte(x, r); }
+};
+template <typename T> struct InLds {             // a quarter held in LDS
+  cplx<T>* q;
+  typedef int Ref;
+  __device__ __forceinline__ Ref ref(int e, int c) const { return e * kBP + c; }
+  __device__ __forceinline__ cplx<T>* at(Ref r) const { return q + r; }
+};
+// The pivot rows' block B of a block update: values and Re + Im (the third
+// real product's operand, formed once here instead of by every row tile).
+template <typename T, int KW> struct PivotRows {
+  cplx<T> v[KW * kBP];
+  T s[KW * kBP];
+};
+
+// ------------------------------------------------------- panel: block update
+// C <- mask(C) + M B on the columns [c0, c0 + cw) (cw <= 32) of one matrix's m
+// listed rows, with M the w <= KW already eliminated columns from j0 on, B
+// their pivot rows' values there (in LDS, [KW][kBP], zero outside w x cw) and
+// the rows whose pivot column pcol lies in [jp, jp + w) masked.  Columns of
+// [skip, skip + w) inside the block are left alone (KW < 32: the eliminated
+// group inside its own quarter).
+// Each wave takes 16 rows x 32 columns at a time and reads M and C straight
+// from memory in the matrix cores' operand layouts, the next step's values in
+// flight while the current one is multiplied: nothing but B goes through LDS
+// and the waves never wait for each other (row tiles staged through LDS with
+// two barriers each reached 50-67% of one compute unit's FP64 matrix rate;
+// rank-8 passes on the vector ALUs with the row's values shuffled between
+// lanes about a quarter).  All loads of a step are waited for after its
+// products and before its stores, so that no load ever waits for a store.
+// FULL: w = KW and cw = 32 (no lane masks, loads that are always issued).
+// Products in the three-product form of the trailing update.
+template <typename T, int KW, bool FULL, typename V>
+__device__ __forceinline__ void block_update_as(const V& x, int m,
+                             const int* __restrict__ pcol, int j0, int jp, int w,
+                             int c0, int cw, int skip,
+                             const PivotRows<T, kNB>& B) {
+  typedef typename Mfma<T>::v4 v4;
+  constexpr int KS = KW < 32 ? KW / 4 : 8;       // k-steps per chunk
+  constexpr int NCH = KW / (4 * KS);
+  static_assert(NCH * KS * 4 == KW, "chunks");
+  const int tid = fresh_tid();
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int li = lane & 15, lk = lane >> 4;
-  const int col = 16 * wc + li;
-  // the tile's M values, its rows' rowcol entries and C values; the next
-  // tile's are loaded while the current one is multiplied (the tiles' rows
-  // are distinct, and the M columns are not written here)
-  cplx<T> mv[kLM];
-  int nrc[RB][4];
-  cplx<T> ncv[RB][4];
-  auto load_tile = [&](int t0) {
-#pragma unroll
-    for (int t = 0; t < kLM; ++t) {
-      const int e = tid + t * kPanelThreads;
-      const int i = e / KW, l = e % KW;
-      mv[t] = x[(size_t)rows[min(t0 + i, m - 1)] * ld + j0 + min(l, w - 1)];
-    }
-#pragma unroll
-    for (int ii = 0; ii < RB; ++ii)
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const int e = t0 + 16 * (RB * wr + ii) + Mfma<T>::drow(lk, v);
-        const int r = rows[min(e, m - 1)];
-        nrc[ii][v] = rowcol[r];
-        ncv[ii][v] = x[(size_t)r * ld + c0 + min(col, cw - 1)];
-      }
+  const bool in0 = FULL || li < cw, in1 = FULL || 16 + li < cw;
+  const bool st0 = in0 && !(KW < 32 && li >= skip && li < skip + w);
+  const bool st1 = in1 && !(KW < 32 && 16 + li >= skip && 16 + li < skip + w);
+  struct CTile {                                 // one tile's C and where it is
+    cplx<T> c[2][4];
+    typename V::Ref at[4];
+    int pc[4];
   };
-  load_tile(0);
-  for (int r0 = 0; r0 < m; r0 += TRW) {
-    __syncthreads();
+  auto load_c = [&](CTile& ct, int t) {
 #pragma unroll
-    for (int t = 0; t < kLM; ++t) {
-      const int e = tid + t * kPanelThreads;
-      const int i = e / KW, l = e % KW;
-      cplx<T> v = mv[t];
-      if (!(r0 + i < m && l < w)) v.re = v.im = T(0);
-      Ms[i * KP + l] = v;
-    }
-    // masked C (pivot rows of the block start from zero); the product is
-    // formed from three real ones (Gauss) as in the trailing update:
-    // P1 = Re a Re b, P2 = Im a Im b, P3 = (Re a + Im a)(Re b + Im b),
-    // Re = P1 - P2, Im = P3 - P1 - P2, and C added afterwards
-    cplx<T> cv[RB][4];
-#pragma unroll
-    for (int ii = 0; ii < RB; ++ii)
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const int e = r0 + 16 * (RB * wr + ii) + Mfma<T>::drow(lk, v);
-        const bool keep = e < m && col < cw &&
-                          !(nrc[ii][v] >= j0 && nrc[ii][v] < j0 + w);
-        cv[ii][v] = ncv[ii][v];
-        if (!keep) cv[ii][v].re = cv[ii][v].im = T(0);
-      }
-    if (r0 + TRW < m) load_tile(r0 + TRW);
-    v4 p1[RB], p2[RB], p3[RB];
-#pragma unroll
-    for (int ii = 0; ii < RB; ++ii)
-#pragma unroll
-      for (int v = 0; v < 4; ++v) p1[ii][v] = p2[ii][v] = p3[ii][v] = T(0);
-    __syncthreads();
-#pragma unroll 4
-    for (int k = 0; k < KW; k += 4) {
-      const cplx<T> b = Bs[(k + lk) * CP + col];
-      const T bs = b.re + b.im;
-#pragma unroll
-      for (int ii = 0; ii < RB; ++ii) {
-        const cplx<T> a = Ms[(16 * (RB * wr + ii) + li) * KP + k + lk];
-        p1[ii] = Mfma<T>::run(a.re, b.re, p1[ii]);
-        p2[ii] = Mfma<T>::run(a.im, b.im, p2[ii]);
-        p3[ii] = Mfma<T>::run(a.re + a.im, bs, p3[ii]);
+    for (int v = 0; v < 4; ++v) {
+      const int e = min(16 * t + Mfma<T>::drow(lk, v), m - 1);
+      ct.at[v] = x.ref(e, c0 + li);
+      ct.pc[v] = pcol[e];
+      if (FULL) {
+        ct.c[0][v] = x.at(ct.at[v])[0];
+        ct.c[1][v] = x.at(ct.at[v])[16];
+      } else {
+        ct.c[0][v].re = ct.c[0][v].im = ct.c[1][v].re = ct.c[1][v].im = T(0);
+        if (in0) ct.c[0][v] = x.at(ct.at[v])[0];
+        if (in1) ct.c[1][v] = x.at(ct.at[v])[16];
       }
     }
+  };
+  auto load_m = [&](cplx<T> (&mn)[KS], int t, int ch) {
+    const int k0 = 4 * KS * ch;
+    const cplx<T>* src = x.at(x.ref(min(16 * t + li, m - 1), j0 + k0 + lk));
 #pragma unroll
-    for (int ii = 0; ii < RB; ++ii)
+    for (int s = 0; s < KS; ++s) {
+      if (FULL) {
+        mn[s] = src[4 * s];
+      } else {
+        mn[s].re = mn[s].im = T(0);
+        if (k0 + 4 * s + lk < w) mn[s] = src[4 * s];
+      }
+    }
+  };
+  const int nt = (m + 15) >> 4;
+  if (wave >= nt) return;
+  // a short product (KW < 32) has the next tile's C in flight too; a long one
+  // covers the latency of its own C, which saves the registers
+  constexpr bool kNextC = KW < 32;
+  cplx<T> a[KS], mn[KS];
+  CTile ct, cn;
+  load_m(a, wave, 0);
+  if (kNextC) load_c(ct, wave);
+#pragma unroll 1
+  for (int t = wave; t < nt; t += kPW) {
+    if (!kNextC) load_c(ct, t);
+    v4 p1[2], p2[2], p3[2];
 #pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const int e = r0 + 16 * (RB * wr + ii) + Mfma<T>::drow(lk, v);
-        if (e < m && col < cw) {
-          const T q1 = p1[ii][v], q2 = p2[ii][v];
-          cplx<T> c;
-          c.re = (q1 - q2) + cv[ii][v].re;
-          c.im = ((p3[ii][v] - q1) - q2) + cv[ii][v].im;
-          x[(size_t)rows[e] * ld + c0 + col] = c;
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) p1[h][v] = p2[h][v] = p3[h][v] = T(0);
+#pragma unroll 1
+    for (int ch = 0; ch < NCH; ++ch) {
+      cplx<T> b[2][2];
+      T bsum[2][2];
+      const int bo = (4 * ch * KS + lk) * kBP + li;
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        b[0][h] = B.v[bo + 16 * h];
+        bsum[0][h] = B.s[bo + 16 * h];
+      }
+      // the next step (past the last one: rows clamped, values unused)
+      if (ch + 1 < NCH) load_m(mn, t, ch + 1);
+      else load_m(mn, t + kPW, 0);
+      if (kNextC) load_c(cn, t + kPW);
+#pragma unroll
+      for (int s = 0; s < KS; ++s) {
+        // the next k-step's B is read during this one's products; the fence
+        // keeps the scheduler from reading all of them at once (registers)
+        if (s + 1 < KS) {
+#pragma unroll
+          for (int h = 0; h < 2; ++h) {
+            b[(s + 1) & 1][h] = B.v[bo + 4 * (s + 1) * kBP + 16 * h];
+            bsum[(s + 1) & 1][h] = B.s[bo + 4 * (s + 1) * kBP + 16 * h];
+          }
         }
+        const T as = a[s].re + a[s].im;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const cplx<T> bb = b[s & 1][h];
+          p1[h] = Mfma<T>::run(a[s].re, bb.re, p1[h]);
+          p2[h] = Mfma<T>::run(a[s].im, bb.im, p2[h]);
+          p3[h] = Mfma<T>::run(as, bsum[s & 1][h], p3[h]);
+        }
+        __builtin_amdgcn_sched_barrier(0);
       }
+      __builtin_amdgcn_s_waitcnt(0x0f70);        // vmcnt(0): every load so far
+#pragma unroll
+      for (int s = 0; s < KS; ++s) a[s] = mn[s];
+    }
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const bool keep = !(ct.pc[v] >= jp && ct.pc[v] < jp + w);
+        const T q1 = p1[h][v], q2 = p2[h][v];
+        ct.c[h][v].re = (q1 - q2) + (keep ? ct.c[h][v].re : T(0));
+        ct.c[h][v].im = ((p3[h][v] - q1) - q2) + (keep ? ct.c[h][v].im : T(0));
+      }
+    if (FULL && 16 * t + 16 <= m) {
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+        if (KW >= 32 || (h ? st1 : st0)) {
+#pragma unroll
+          for (int v = 0; v < 4; ++v) x.at(ct.at[v])[16 * h] = ct.c[h][v];
+        }
+    } else {
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+          if ((h ? st1 : st0) && 16 * t + Mfma<T>::drow(lk, v) < m)
+            x.at(ct.at[v])[16 * h] = ct.c[h][v];
+    }
+    if (kNextC) ct = cn;
+  }
+}
+template <typename T, int KW, typename V>
+__device__ __forceinline__ void block_update(const V& x, int m,
+                             const int* __restrict__ pcol, int j0, int jp, int w,
+                             int c0, int cw, int skip,
+                             const PivotRows<T, kNB>& B) {
+  if (w == KW && cw == 32)
+    block_update_as<T, KW, true>(x, m, pcol, j0, jp, w, c0, cw, skip, B);
+  else
+    block_update_as<T, KW, false>(x, m, pcol, j0, jp, w, c0, cw, skip, B);
+}
+
+// B of block_update: row l, column c = value of list entry pive[l] (the pivot
+// row of column l) in column c0 + c, zero outside w x cw and in
+// [skip, skip + w) (skip < 0: none).
+template <typename T, int KW, typename V>
+__device__ __forceinline__ void load_pivot_rows(const V& x, const int* pive, int w, int c0,
+                             int cw, int skip, PivotRows<T, kNB>& B) {
+  const int tid = fresh_tid();
+#pragma unroll
+  for (int e0 = 0; e0 < KW * 32; e0 += kPanelThreads) {
+    const int e = e0 + tid;
+    if (KW * 32 >= kPanelThreads || e < KW * 32) {
+      const int l = e >> 5, c = e & 31;
+      cplx<T> v = *x.at(x.ref(pive[min(l, w - 1)], c0 + min(c, cw - 1)));
+      if (!(l < w && c < cw) || (skip >= 0 && c >= skip && c < skip + w))
+        v.re = v.im = T(0);
+      B.v[l * kBP + c] = v;
+      B.s[l * kBP + c] = v.re + v.im;
+    }
   }
 }
 
-// ---------------------------------------------------- panel: factorization
-// Eliminate the PW (32) columns starting at c0 on the listed rows
-// rows[0, m) (the rows not pivoted before this outer block) with partial
-// pivoting, IB columns at a time in registers.  Thread tid owns list entries
-// tid + i * kPanelThreads, i < RPT; the list is in ascending row order, so a
-// tie of pivot keys goes to the lowest row index.
-template <typename T, int PW, int RPT, int IB>
-__device__ __forceinline__ void factor_panel(cplx<T>* __restrict__ x, int ld, int n,
-                             const int* __restrict__ rows, int m,
-                             int* __restrict__ piv, int* __restrict__ rowcol,
-                             int c0, int* __restrict__ status,
-                             unsigned char* smem) {
-  static_assert(PW % IB == 0 && PW <= kNB, "panel width");
-  cplx<T>* Bo = reinterpret_cast<cplx<T>*>(smem);   // [IB][PW]
-  // pivot row and the waves' pivot candidates, double-buffered by column
-  // parity so one column's reads never meet the next column's writes
-  cplx<T>* prow2 = Bo + IB * PW;                     // [2][IB]
-  T* redv2 = reinterpret_cast<T*>(prow2 + 2 * IB);   // [2][kPW]
-  int* redi2 = reinterpret_cast<int*>(redv2 + 2 * kPW);  // [2][kPW]
-  int* pvt = redi2 + 2 * kPW;                        // [IB]
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int cw = min(PW, n - c0);
-  const T inf_key = big_value<T>();
+// -------------------------------------------------- panel: column elimination
+// LDS of one group's pivot search: each wave's candidate (key with place, and
+// the row's values), double-buffered by column parity so that one column's
+// reads never meet the next column's writes.
+template <typename T, int IB> struct Candidates {
+  cplx<T> row[2][kPW][IB];
+  int key[2][kPW];
+};
 
-  // bit i: list entry tid + i kPanelThreads is pivoted (or absent); row ids
-  // are re-read from the LDS list where needed (registers go to v)
-  unsigned pvd = 0u;
-  static_assert(RPT <= 32, "pivot bits");
+// The group's IB columns of the thread's rows, loaded and stored with the
+// lanes along the rows (IB lanes per row, whole cache lines per access) and
+// transposed through a wave's own part of LDS: one row per lane would touch 64
+// lines per access, and a load or store of a group then costs as much as
+// eliminating it.  pos(i): first list entry of the wave's i-th 64 rows.
+template <typename T, int RPT, int IB>
+__device__ __forceinline__ void load_group(const InMemory<T>& x, int m, int c, int iw,
+                                           int tid, cplx<T>* stage, cplx<T> (&v)[RPT][IB]) {
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  constexpr int RL = 64 / IB, P = IB + 1;        // rows per access, LDS pitch
+  cplx<T>* sw = stage + wave * 64 * P;
+  const int lr = lane / IB, lc = lane % IB;
+#pragma unroll
+  for (int i = 0; i < RPT; ++i) {
+    const int e0 = wave * 64 + i * kPanelThreads;
+    if (e0 < m) {                                // the same for the whole wave
+      cplx<T> t[IB];
+#pragma unroll
+      for (int j = 0; j < IB; ++j) {
+        t[j].re = t[j].im = T(0);
+        const int e = e0 + j * RL + lr;
+        if (e < m && lc < iw) t[j] = *x.at(x.ref(e, c + lc));
+      }
+#pragma unroll
+      for (int j = 0; j < IB; ++j) sw[(j * RL + lr) * P + lc] = t[j];
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // within the wave
+#pragma unroll
+      for (int l = 0; l < IB; ++l) v[i][l] = sw[lane * P + l];
+    } else {
+#pragma unroll
+      for (int l = 0; l < IB; ++l) v[i][l].re = v[i][l].im = T(0);
+    }
+  }
+}
+template <typename T, int RPT, int IB>
+__device__ __forceinline__ void store_group(const InMemory<T>& x, int m, int c, int iw,
+                                            int tid, cplx<T>* stage,
+                                            const cplx<T> (&v)[RPT][IB]) {
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  constexpr int RL = 64 / IB, P = IB + 1;
+  cplx<T>* sw = stage + wave * 64 * P;
+  const int lr = lane / IB, lc = lane % IB;
+#pragma unroll
+  for (int i = 0; i < RPT; ++i) {
+    const int e0 = wave * 64 + i * kPanelThreads;
+    if (e0 < m) {
+#pragma unroll
+      for (int l = 0; l < IB; ++l) sw[lane * P + l] = v[i][l];
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+#pragma unroll
+      for (int j = 0; j < IB; ++j) {
+        const int e = e0 + j * RL + lr;
+        if (e < m && lc < iw) *x.at(x.ref(e, c + lc)) = sw[(j * RL + lr) * P + lc];
+      }
+    }
+  }
+}
+template <typename T, int RPT, int IB>
+__device__ __forceinline__ void load_group(const InLds<T>& x, int m, int c, int iw,
+                                           int tid, cplx<T>*, cplx<T> (&v)[RPT][IB]) {
 #pragma unroll
   for (int i = 0; i < RPT; ++i) {
     const int e = tid + i * kPanelThreads;
-    if (!(e < m) || rowcol[rows[min(e, m - 1)]] >= 0) pvd |= 1u << i;
-  }
-  const int ngroups = (cw + IB - 1) / IB;
-
-  for (int b0 = 0; b0 < cw; b0 += IB) {
-    const int iw = min(IB, cw - b0);
-    cplx<T> v[RPT][IB];
-#pragma unroll
-    for (int i = 0; i < RPT; ++i) {
-#pragma unroll
-      for (int l = 0; l < IB; ++l)
-        v[i][l] = x[(size_t)rows[min(tid + i * kPanelThreads, m - 1)] * ld + c0 + b0 +
-                    min(l, iw - 1)];
-    }
-#pragma unroll
-    for (int i = 0; i < RPT; ++i) {
-      const int e = tid + i * kPanelThreads;
-#pragma unroll
-      for (int l = 0; l < IB; ++l)
-        if (!(e < m && l < iw)) v[i][l].re = v[i][l].im = T(0);
-    }
 #pragma unroll
     for (int l = 0; l < IB; ++l) {
-      if (l >= iw) break;
-      cplx<T>* prow = prow2 + (l & 1) * IB;
-      T* redv = redv2 + (l & 1) * kPW;
-      int* redi = redi2 + (l & 1) * kPW;
-      // ---- pivot search: largest |re|+|im| among unpivoted rows (bidx is
-      // a list index)
-      T best = T(-1);
-      int bidx = INT_MAX;
-#pragma unroll
-      for (int i = 0; i < RPT; ++i) {
-        const int e = tid + i * kPanelThreads;
-        if (e < m && !((pvd >> i) & 1u)) {
-          T a = fabs(v[i][l].re) + fabs(v[i][l].im);
-          if (!(a <= inf_key)) a = inf_key;  // NaN / Inf win and get flagged
-          if (a > best || (a == best && e < bidx)) {
-            best = a;
-            bidx = e;
-          }
-        }
-      }
-#pragma unroll
-      for (int off = 32; off >= 1; off >>= 1) {
-        const T ob = __shfl_xor(best, off);
-        const int oi = __shfl_xor(bidx, off);
-        if (ob > best || (ob == best && oi < bidx)) {
-          best = ob;
-          bidx = oi;
-        }
-      }
-      if (lane == 0) {
-        redv[wave] = best;
-        redi[wave] = bidx;
-      }
-      __syncthreads();
-      best = redv[0];
-      bidx = redi[0];
-#pragma unroll
-      for (int wv = 1; wv < kPW; ++wv) {
-        const T ob = redv[wv];
-        const int oi = redi[wv];
-        if (ob > best || (ob == best && oi < bidx)) {
-          best = ob;
-          bidx = oi;
-        }
-      }
-      // a valid unpivoted entry: the list holds more rows than this block
-      // has columns
-      const int pe = bidx;
-      const int p = rows[min(pe, m - 1)];
-      const int col = c0 + b0 + l;
-      if (tid == 0 && (best == T(0) || best == inf_key))
-        atomicCAS(status, 0, best == T(0) ? (1 + col) : -(1 + col));
-      if ((pe % kPanelThreads) == tid) {
-        const int i = pe / kPanelThreads;
-#pragma unroll
-        for (int ii = 0; ii < RPT; ++ii)
-          if (ii == i) {
-#pragma unroll
-            for (int l2 = 0; l2 < IB; ++l2) prow[l2] = v[ii][l2];
-            pvd |= 1u << ii;
-          }
-        piv[col] = p;
-        rowcol[p] = col;
-        pvt[l] = p;
-      }
-      __syncthreads();
-      // ---- eliminate column l from every other row (Gauss-Jordan)
-      const cplx<T> pv = prow[l];
-      const T den = pv.re * pv.re + pv.im * pv.im;
-      cplx<T> inv;
-      inv.re = pv.re / den;
-      inv.im = -pv.im / den;
-      // column by column of the register block: the scaled pivot row entry is
-      // formed from LDS as it is used (RPT multipliers in registers instead of
-      // IB scaled entries; fewer spills in both panel shapes)
-      cplx<T> mi[RPT];
-#pragma unroll
-      for (int i = 0; i < RPT; ++i) mi[i] = v[i][l];
-#pragma unroll
-      for (int l2 = 0; l2 < IB; ++l2) {
-        if (l2 == l) continue;
-        const cplx<T> q = cmul(prow[l2], inv);
-#pragma unroll
-        for (int i = 0; i < RPT; ++i) {
-          if (tid + i * kPanelThreads == pe) {
-            v[i][l2] = q;
-          } else {
-            v[i][l2].re -= mi[i].re * q.re - mi[i].im * q.im;
-            v[i][l2].im -= mi[i].re * q.im + mi[i].im * q.re;
-          }
-        }
-      }
-#pragma unroll
-      for (int i = 0; i < RPT; ++i) {
-        if (tid + i * kPanelThreads == pe) {
-          v[i][l] = inv;
-        } else {
-          const cplx<T> nm = cmul(mi[i], inv);
-          v[i][l].re = -nm.re;
-          v[i][l].im = -nm.im;
-        }
-      }
+      v[i][l].re = v[i][l].im = T(0);
+      if (e < m && l < iw) v[i][l] = *x.at(x.ref(e, c + l));
     }
-    // ---- write the eliminated block back; old pivot rows of the other columns
+  }
+}
+template <typename T, int RPT, int IB>
+__device__ __forceinline__ void store_group(const InLds<T>& x, int m, int c, int iw,
+                                            int tid, cplx<T>*, const cplx<T> (&v)[RPT][IB]) {
 #pragma unroll
-    for (int i = 0; i < RPT; ++i) {
-      const int e = tid + i * kPanelThreads;
-      if (e < m) {
+  for (int i = 0; i < RPT; ++i) {
+    const int e = tid + i * kPanelThreads;
 #pragma unroll
-        for (int l = 0; l < IB; ++l)
-          if (l < iw) x[(size_t)rows[e] * ld + c0 + b0 + l] = v[i][l];
-      }
-    }
-    for (int e = tid; e < IB * PW; e += kPanelThreads) {
-      const int l = e / PW, c = e % PW;
-      const bool ok = l < iw && c < cw && (c < b0 || c >= b0 + iw);
-      cplx<T> t = x[(size_t)pvt[min(l, iw - 1)] * ld + c0 + min(c, cw - 1)];
-      if (!ok) t.re = t.im = T(0);
-      Bo[e] = t;
-    }
-    __syncthreads();
-    // ---- rank-iw update of the other column groups of the panel: 16 lanes
-    // per row (lane k holds columns k and k + 16 of the panel), four rows per
-    // wave at a time, so each load and store of a wave covers four rows'
-    // contiguous segments instead of one cache line per lane; a row's
-    // eliminated values come from the lanes holding them (16-wide shuffles).
-    if (ngroups > 1) {
-      static_assert(PW == 32 && 16 % IB == 0, "panel lane map");
-      const int k16 = lane & 15, rr = lane >> 4;
-      const int ca = k16, cb = k16 + 16;
-      const bool sta = ca < cw && !(ca >= b0 && ca < b0 + IB);
-      const bool stb = cb < cw && !(cb >= b0 && cb < b0 + IB);
-      cplx<T> boa[IB], bob[IB];
-      int pv0[IB];
-#pragma unroll
-      for (int l = 0; l < IB; ++l) {
-        boa[l] = Bo[l * PW + ca];
-        bob[l] = Bo[l * PW + cb];
-        pv0[l] = (l < iw) ? pvt[l] : -1;
-      }
-      const int src0 = b0 & 15;          // lane holding column b0 of the row
-      const bool hi = b0 >= 16;          // ... in its second value
-      // kRU groups of four rows per wave and trip: their loads are issued
-      // together, so a wave waits for memory once per kRU groups (the rows
-      // of a trip are distinct; each is read and written by one lane group)
-      constexpr int kRU = 4, kStep = 4 * kPW;
-#pragma unroll 1
-      for (int e0 = 4 * wave; e0 < m; e0 += kStep * kRU) {
-        int r[kRU];
-        cplx<T> va[kRU], vb[kRU];
-#pragma unroll
-        for (int u = 0; u < kRU; ++u) r[u] = rows[min(e0 + kStep * u + rr, m - 1)];
-#pragma unroll
-        for (int u = 0; u < kRU; ++u) {
-          va[u] = x[(size_t)r[u] * ld + c0 + min(ca, cw - 1)];
-          vb[u] = x[(size_t)r[u] * ld + c0 + min(cb, cw - 1)];
-        }
-#pragma unroll
-        for (int u = 0; u < kRU; ++u) {
-          const int e = e0 + kStep * u + rr;
-          bool isp = false;
-#pragma unroll
-          for (int l = 0; l < IB; ++l) isp |= (pv0[l] == r[u]);
-          cplx<T> acca = va[u], accb = vb[u];
-          if (isp) acca.re = acca.im = accb.re = accb.im = T(0);
-          const cplx<T> src = hi ? vb[u] : va[u];
-#pragma unroll
-          for (int l = 0; l < IB; ++l) {
-            if (l < iw) {
-              cplx<T> mm;
-              mm.re = __shfl(src.re, src0 + l, 16);
-              mm.im = __shfl(src.im, src0 + l, 16);
-              cfma(acca, mm, boa[l]);
-              cfma(accb, mm, bob[l]);
-            }
-          }
-          if (e < m) {
-            if (sta) x[(size_t)r[u] * ld + c0 + ca] = acca;
-            if (stb) x[(size_t)r[u] * ld + c0 + cb] = accb;
-          }
-        }
-      }
-    }
-    __syncthreads();
+    for (int l = 0; l < IB; ++l)
+      if (e < m && l < iw) *x.at(x.ref(e, c + l)) = v[i][l];
   }
 }
 
-// LDS of the panel kernel: the larger of the two phases' buffers, then the
-// list of the rows the block works on.
-template <typename T> __host__ __device__ constexpr size_t panel_body_bytes() {
-  return ((sizeof(cplx<T>) * (size_t)(kNB + kTile) * kPitch >
-                   sizeof(cplx<T>) * (kIB * kNB + 2 * kIB) + 2 * kPW * sizeof(T) +
-                       2 * kPW * sizeof(int) + kIB * sizeof(int)
-               ? sizeof(cplx<T>) * (size_t)(kNB + kTile) * kPitch
-               : sizeof(cplx<T>) * (kIB * kNB + 2 * kIB) + 2 * kPW * sizeof(T) +
-                     2 * kPW * sizeof(int) + kIB * sizeof(int)) + 15) / 16 * 16;
-}
-template <typename T> static size_t panel_lds_bytes(int rpt) {
-  return panel_body_bytes<T>() + sizeof(int) * (size_t)rpt * kPanelThreads;
+// Eliminate IB columns in registers on the m <= CAP listed rows, with partial
+// pivoting; thread tid owns list entries tid + i kPanelThreads, i < RPT, and
+// place[i] counts them down (-1 once that entry is pivoted, or if absent).
+// The columns are c .. in the frame of x and ca .. of the matrix.
+// A key holds the upper bits of |re| + |im| and the row's place, so that one
+// integer maximum yields the pivot and where it is; it leaves at least 7
+// mantissa bits (9 up to 2048 rows, 11 up to 512), which bounds the
+// multipliers by 1 + 2^-7 instead of 1, and equal keys go to the lowest row.
+// One barrier per column: every wave publishes its best candidate together
+// with the candidate's row, so that the row is in LDS when the winner is
+// known.  The chain per column bounds it (maximum over the wave's lanes,
+// publication, barrier, the reciprocal: about 1000 cycles), so the next
+// column's maximum runs beside the rest of the row update, waves without rows
+// only take part in the barrier, and RPT is chosen by the rows left.
+// The column loop is not unrolled: each step writes a row's columns one slot
+// down as it updates them, so that the column to eliminate is always slot 0
+// (the row is back in order after IB steps).
+template <typename T, int RPT, int IB, int CAP, typename V>
+__device__ __forceinline__ void eliminate_columns(const V& x, const int* rows, int m,
+                             int c, int ca, int iw, int (&place)[RPT],
+                             int* __restrict__ piv, int* __restrict__ rowcol, int* pcol,
+                             int* pive, int* __restrict__ status, cplx<T>* stage,
+                             Candidates<T, IB>& cd) {
+  constexpr int kPlace = place_mask(CAP);
+  const int tid = fresh_tid(), lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const bool any = wave * 64 < m;                // this wave holds rows
+  cplx<T> v[RPT][IB];
+  if (any) load_group<T, RPT, IB>(x, m, c, iw, tid, stage, v);
+  else if (lane == 0) cd.key[0][wave] = cd.key[1][wave] = -1;
+  auto thread_best = [&]() {
+    int b = -1;
+#pragma unroll
+    for (int i = 0; i < RPT; ++i)
+      b = max(b, (pivot_key(v[i][0]) & ~kPlace) | place[i]);
+    return b;
+  };
+  int best = thread_best(), wmax = any ? max_of_wave(best) : -1;
+#pragma unroll 1
+  for (int l = 0; l < iw; ++l) {
+    const int par = l & 1;
+    if (any) {
+      if (wmax >= 0 ? best == wmax : lane == 0) {      // one lane
+        cd.key[par][wave] = wmax;
+        const int wi = (kPlace - (wmax & kPlace)) / kPanelThreads;   // uniform
+#pragma unroll
+        for (int i = 0; i < RPT; ++i)
+          if (i == wi) {
+#pragma unroll
+            for (int q = 0; q < IB; ++q) cd.row[par][wave][q] = v[i][q];
+          }
+      }
+    }
+    __syncthreads();
+    if (!any) continue;
+    // ---- the block's pivot, from the kPW candidates
+    int gmax = cd.key[par][0];
+#pragma unroll
+    for (int q = 1; q < kPW; ++q) gmax = max(gmax, cd.key[par][q]);
+    gmax = __builtin_amdgcn_readfirstlane(gmax);
+    // a valid unpivoted entry: the list holds at least as many rows as this
+    // block has columns
+    const int pe = kPlace - (gmax & kPlace);
+    const int win = (pe & (kPanelThreads - 1)) >> 6, pi = pe / kPanelThreads;
+    cplx<T> prow[IB];
+#pragma unroll
+    for (int q = 0; q < IB; ++q) prow[q] = cd.row[par][win][q];
+    const T den = T(1) / (prow[0].re * prow[0].re + prow[0].im * prow[0].im);
+    cplx<T> inv;
+    inv.re = prow[0].re * den;
+    inv.im = -prow[0].im * den;
+    const bool mine = (pe & (kPanelThreads - 1)) == tid;
+    if (mine) {
+      const int e = min(pe, m - 1), p = rows[e];
+      piv[ca + l] = p;
+      rowcol[p] = ca + l;
+      pcol[e] = ca + l;
+      pive[l] = e;
+      const bool zero = prow[0].re == T(0) && prow[0].im == T(0);
+      if (zero || gmax >= (bad_key<T>() & ~kPlace))
+        atomicCAS(status, 0, zero ? (1 + ca + l) : -(1 + ca + l));
+    }
+    // ---- eliminate the column from every other row (Gauss-Jordan): row <-
+    // row - t prow with t = row[0] / pivot and -t in this column's place.  The
+    // pivot row itself becomes prow / pivot: the same update of a zero row
+    // with t = -1 / pivot.
+    auto update = [&](int i, const cplx<T>& t, int q) {
+      v[i][q - 1].re = fma(t.im, prow[q].im, fma(-t.re, prow[q].re, v[i][q].re));
+      v[i][q - 1].im = fma(-t.im, prow[q].re, fma(-t.re, prow[q].im, v[i][q].im));
+    };
+    // (many rows per thread: no registers to keep every t)
+    constexpr bool kOverlap = RPT <= 4;
+    cplx<T> t[RPT];
+#pragma unroll
+    for (int i = 0; i < RPT; ++i) {
+      t[i] = cmul(v[i][0], inv);
+      if (mine && i == pi) {
+        place[i] = -1;
+        t[i].re = -inv.re;
+        t[i].im = -inv.im;
+#pragma unroll
+        for (int q = 1; q < IB; ++q) v[i][q].re = v[i][q].im = T(0);
+      }
+      update(i, t[i], 1);
+      if (!kOverlap) {
+#pragma unroll
+        for (int q = 2; q < IB; ++q) update(i, t[i], q);
+        v[i][IB - 1].re = -t[i].re;
+        v[i][IB - 1].im = -t[i].im;
+      }
+    }
+    best = thread_best();
+    wmax = max_of_wave(best);
+    if (kOverlap) {
+#pragma unroll
+      for (int i = 0; i < RPT; ++i) {
+#pragma unroll
+        for (int q = 2; q < IB; ++q) update(i, t[i], q);
+        v[i][IB - 1].re = -t[i].re;
+        v[i][IB - 1].im = -t[i].im;
+      }
+    }
+  }
+#pragma unroll 1
+  for (int l = iw; l < IB; ++l)   // a short group: back in order
+#pragma unroll
+    for (int i = 0; i < RPT; ++i) {
+      const cplx<T> f = v[i][0];
+#pragma unroll
+      for (int q = 1; q < IB; ++q) v[i][q - 1] = v[i][q];
+      v[i][IB - 1] = f;
+    }
+  if (any) store_group<T, RPT, IB>(x, m, c, iw, tid, stage, v);
 }
 
 // Outer block S of one matrix.  Rows pivoted in earlier blocks take no part:
 // their columns of this block follow from the block's pivot rows afterwards
-// (k_fix), so the panel reads and writes only the n - S kNBO remaining rows.
-// RPT kPanelThreads >= n rows; IB columns eliminated in registers at a time.
-template <typename T, int RPT, int IB>
+// (k_fix), so the panel reads and writes only the n - S kNBO remaining rows,
+// at most RPT kPanelThreads.  Four 32-column quarters; each eliminates groups
+// of IB columns in registers, whose transform then updates the quarter's
+// other columns (block_update with KW = IB), and is joined to the other
+// quarter of its 64-column half and the halves to each other by updates with
+// KW = 32 and 64.  QR > 0: at most QR rows; the quarter is kept in LDS while
+// it is factored, so that its groups meet LDS latencies instead of memory's.
+template <typename T, int RPT, int IB, int QR>
 __global__ __launch_bounds__(kPanelThreads, 1) void k_outer_panel(
     cplx<T>* __restrict__ xbuf, int* __restrict__ pivbuf,
     int* __restrict__ rowcolbuf, const MatDesc* __restrict__ descs, int S,
     int* __restrict__ status) {
-  extern __shared__ __align__(16) unsigned char smem[];
+  constexpr int kCap = QR > 0 ? QR : RPT * kPanelThreads;
+  static_assert(kCap <= RPT * kPanelThreads, "panel rows");
+  __shared__ PivotRows<T, kNB> B;
+  __shared__ Candidates<T, IB> cd;
+  // a wave's transpose buffers, or the quarter
+  __shared__ cplx<T> stage[QR > 0 ? QR * kBP : kPW * 64 * (IB + 1)];
+  __shared__ int rows[kCap];
+  __shared__ unsigned roff[kCap];   // byte offset of each entry's row
+  __shared__ int pcol[kCap];     // pivot column of each list entry, or -1
+  __shared__ int pive[kNBO];     // list entry of each column's pivot row
+  __shared__ int cnt[2][kPW];
   const MatDesc d = descs[blockIdx.x];
   const int n = d.n;
-  if (S * kNBO >= n) return;
-  cplx<T>* x = xbuf + d.xoff;
+  const int J0 = S * kNBO;
+  if (J0 >= n) return;
   int* piv = pivbuf + d.ioff;
   int* rowcol = rowcolbuf + d.ioff;
   int* st = status + d.status_idx;
 
-  // list the unpivoted rows in ascending order (wave ballots, then offsets)
-  int* rows = reinterpret_cast<int*>(smem + panel_body_bytes<T>());
-  int* cnt = reinterpret_cast<int*>(smem);   // [RPT][kPW], before the panel
+  // list the unpivoted rows in ascending order (wave ballots, then offsets);
+  // m = n - J0 <= kCap: every earlier column pivoted one row
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  unsigned long long bal[RPT];
+  int m = 0;
+  for (int r0 = 0, b = 0; r0 < n; r0 += kPanelThreads, b ^= 1) {
+    const int r = r0 + tid;
+    const unsigned long long bal = __ballot(r < n && rowcol[min(r, n - 1)] < 0);
+    if (lane == 0) cnt[b][wave] = (int)__popcll(bal);
+    __syncthreads();
+    int pos = m + (int)__popcll(bal & ((1ull << lane) - 1ull));
 #pragma unroll
-  for (int i = 0; i < RPT; ++i) {
-    const int r = tid + i * kPanelThreads;
-    bal[i] = __ballot(r < n && rowcol[min(r, n - 1)] < 0);
-    if (lane == 0) cnt[i * kPW + wave] = (int)__popcll(bal[i]);
+    for (int q = 0; q < kPW; ++q) {
+      const int k = cnt[b][q];
+      pos += q < wave ? k : 0;
+      m += k;
+    }
+    if (((bal >> lane) & 1ull) && pos < kCap) {
+      rows[pos] = r;
+      roff[pos] = (unsigned)r * (unsigned)d.ld * (unsigned)sizeof(cplx<T>);
+      pcol[pos] = -1;
+    }
   }
-  __syncthreads();
-  int m = 0;   // n - S kNBO unless earlier blocks failed to pivot
-  int pos[RPT];
-#pragma unroll
-  for (int i = 0; i < RPT; ++i) {
-    int before = 0;
-#pragma unroll
-    for (int wv = 0; wv < kPW; ++wv) before += (wv < wave) ? cnt[i * kPW + wv] : 0;
-    pos[i] = m + before + (int)__popcll(bal[i] & ((1ull << lane) - 1ull));
-#pragma unroll
-    for (int wv = 0; wv < kPW; ++wv) m += cnt[i * kPW + wv];
-  }
-#pragma unroll
-  for (int i = 0; i < RPT; ++i)
-    if ((bal[i] >> lane) & 1ull) rows[pos[i]] = tid + i * kPanelThreads;
+  m = min(m, kCap);
   __syncthreads();
   if (m == 0) return;   // the same for every thread
 
-  // Each 64-column half as two 32-column quarters joined by cross updates,
-  // then the halves joined the same way.  Order: Q0, Q0->Q1, Q1, Q1->Q0,
-  // L->R, Q2, Q2->Q3, Q3, Q3->Q2, R->L (one call site per kind of step).
-  const int ld = d.ld;
-  const int J0 = S * kNBO, J1 = J0 + kNB;
-#pragma unroll 1
-  for (int qi = 0; qi < 4; ++qi) {
-    const int c = J0 + 32 * qi;
-    if (c >= n) break;
-    if (qi == 2) {
-      cross_update<T, kNB, kNB>(x, ld, rows, m, piv, rowcol, J0, kNB, J1,
-                                min(kNB, n - J1), smem);
-      __syncthreads();
-    }
-    factor_panel<T, 32, RPT, IB>(x, ld, n, rows, m, piv, rowcol, c, st, smem);
-    __syncthreads();
-    const int dst = (qi & 1) ? c - 32 : c + 32;
-    if (dst < n) {
-      cross_update<T, 32, 32>(x, ld, rows, m, piv, rowcol, c, min(32, n - c),
-                              dst, min(32, n - dst), smem);
-      __syncthreads();
-    }
+  int place[RPT];                // see eliminate_columns
+#pragma unroll
+  for (int i = 0; i < RPT; ++i) {
+    const int e = tid + i * kPanelThreads;
+    place[i] = e < m ? place_mask(kCap) - e : -1;
   }
-  if (J1 < n)
-    cross_update<T, kNB, kNB>(x, ld, rows, m, piv, rowcol, J1, min(kNB, n - J1),
-                              J0, kNB, smem);
+
+  const int J1 = J0 + kNB;
+  const InMemory<T> x{xbuf + d.xoff, roff};
+  // update the columns [c0, c0 + cw) with the transform of [j0, j0 + w); the
+  // barriers order it after the writes before it and before the reads after
+  auto cross32 = [&](int j0, int w, int c0, int cw) {
+    load_pivot_rows<T, 32>(x, pive + (j0 - J0), w, c0, cw, -1, B);
+    __syncthreads();
+    block_update<T, 32>(x, m, pcol, j0, j0, w, c0, cw, 0, B);
+    __syncthreads();
+  };
+  auto cross64 = [&](int j0, int w, int c0) {
+#pragma unroll 1
+    for (int c = c0; c < min(c0 + kNB, n); c += 32) {
+      load_pivot_rows<T, kNB>(x, pive + (j0 - J0), w, c, min(32, n - c), -1, B);
+      __syncthreads();
+      block_update<T, kNB>(x, m, pcol, j0, j0, w, c, min(32, n - c), 0, B);
+      __syncthreads();
+    }
+  };
+  // factor the quarter [c0, c0 + cw), whose columns start at f in the frame
+  auto quarter = [&](const auto& view, int f, int c0, int cw) {
+#pragma unroll 1
+    for (int b0 = 0; b0 < cw; b0 += IB) {
+      const int iw = min(IB, cw - b0);
+      int* pe = pive + (c0 - J0) + b0;
+      eliminate_columns<T, RPT, IB, kCap>(view, rows, m, f + b0, c0 + b0, iw, place, piv,
+                                          rowcol, pcol, pe, st, stage, cd);
+      __syncthreads();   // pive, pcol and the eliminated columns
+      if (cw > IB) {
+        load_pivot_rows<T, IB>(view, pe, iw, f, cw, b0, B);
+        __syncthreads();
+        block_update<T, IB>(view, m, pcol, f + b0, c0 + b0, iw, f, cw, b0, B);
+        __syncthreads();
+      }
+    }
+  };
+  auto copy_quarter = [&](int c0, int cw, bool out) {
+    for (int e = tid; e < 32 * m; e += kPanelThreads) {
+      const int r = e >> 5, c = e & 31;
+      if (c < cw) {
+        if (out) *x.at(x.ref(r, c0 + c)) = stage[r * kBP + c];
+        else stage[r * kBP + c] = *x.at(x.ref(r, c0 + c));
+      }
+    }
+    __syncthreads();
+  };
+#pragma unroll 1
+  for (int qi = 0; qi < 6; ++qi) {
+    // steps 0, 1, 3, 4: the quarters; 2 and 5: left half to right and back
+    if (qi == 2 || qi == 5) {
+      const int j0 = qi == 2 ? J0 : J1, c0 = qi == 2 ? J1 : J0;
+      if (J1 < n) cross64(j0, min(kNB, n - j0), c0);
+      continue;
+    }
+    const int qq = qi < 2 ? qi : qi - 1;
+    const int c0 = J0 + 32 * qq;
+    if (c0 >= n) continue;
+    const int cw = min(32, n - c0);
+    if constexpr (QR > 0) {
+      copy_quarter(c0, cw, false);
+      quarter(InLds<T>{stage}, 0, c0, cw);
+      copy_quarter(c0, cw, true);
+    } else {
+      quarter(x, c0, c0, cw);
+    }
+    const int dst = (qq & 1) ? c0 - 32 : c0 + 32;
+    if (dst < n) cross32(c0, cw, dst, min(32, n - dst));
+  }
 }
 
 // ------------------------------------------------------------------ gather
@@ -746,33 +869,23 @@ __global__ __launch_bounds__(128 * WR, 4 / WR) void k_update(
 template <typename T>
 hipError_t gje_panel(cplx<T>* x, int* piv, int* rowcol, const MatDesc* d,
                      int nmat, int nmax, int S, int* status, hipStream_t st) {
-  // the dynamic-LDS limit is a per-device attribute of each kernel: set once
-  // per device (outside any graph capture: the first call on a device may
-  // pass nmat = 0 for just this)
-  static std::atomic<unsigned> attr_set{0u};
-  int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess) return hipErrorInvalidDevice;
-  const unsigned bit = dev < 32 ? (1u << dev) : 0u;
-  const size_t lds_s = panel_lds_bytes<T>(kRPTs), lds_l = panel_lds_bytes<T>(kRPTl);
-  if (!bit || !(attr_set.load() & bit)) {
-    hipError_t e = hipFuncSetAttribute(
-        reinterpret_cast<const void*>(&k_outer_panel<T, kRPTs, kIBs>),
-        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_s);
-    if (e == hipSuccess)
-      e = hipFuncSetAttribute(
-          reinterpret_cast<const void*>(&k_outer_panel<T, kRPTl, kIBl>),
-          hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_l);
-    if (e != hipSuccess) return e;
-    attr_set.fetch_or(bit);
-  }
-  if (nmat <= 0) return hipSuccess;
+  const int left = nmax - S * kNBO;    // rows left of the largest matrix
+  if (nmat <= 0 || left <= 0) return hipSuccess;
   if (nmax > kMaxN) return hipErrorInvalidValue;
-  if (nmax <= kSmallN)
-    hipLaunchKernelGGL((k_outer_panel<T, kRPTs, kIBs>), dim3(nmat), dim3(kPanelThreads),
-                       lds_s, st, x, piv, rowcol, d, S, status);
-  else
-    hipLaunchKernelGGL((k_outer_panel<T, kRPTl, kIBl>), dim3(nmat), dim3(kPanelThreads),
-                       lds_l, st, x, piv, rowcol, d, S, status);
+  auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(nmat), dim3(kPanelThreads), 0, st, x, piv, rowcol, d,
+                       S, status);
+  };
+  // by the rows left: quarters of at most 192 (complex64 448) rows stay in
+  // LDS; then one, two or four rows per thread; beyond 2048 rows four columns
+  // per register block keep the rows in registers
+  if (left <= 192) go(k_outer_panel<T, 1, kIB, 192>);
+  else if (left <= 448 && sizeof(T) == 4) go(k_outer_panel<T, 1, kIB, sizeof(T) == 4 ? 448 : 0>);
+  else if (left <= kPanelThreads) go(k_outer_panel<T, 1, kIB, 0>);
+  else if (left <= 2 * kPanelThreads) go(k_outer_panel<T, 2, kIB, 0>);
+  else if (left <= 4 * kPanelThreads) go(k_outer_panel<T, 4, kIB, 0>);
+  else if (left <= 6 * kPanelThreads) go(k_outer_panel<T, 6, 4, 0>);
+  else go(k_outer_panel<T, kMaxN / kPanelThreads, 4, 0>);
   return hipGetLastError();
 }
 

@@ -45,3 +45,43 @@ def test_tile_and_chunk_edges(lib, n_c):
         ctx.set_refinement(1)
         ctx.compute_gloc(lib.FK_MIXED)
         assert relerr(ctx.get_gloc(), go) < 1e-8
+
+
+# rows left of a block pick the panel's form: 192 (448 in complex64) rows in
+# LDS, 512, 1024, 2048, 3072 and more rows in registers; the first block of
+# n_c rows sits on each side of a line, the later ones cross the ones below
+@pytest.mark.parametrize("n_c", [1, 0, -1])
+@pytest.mark.parametrize("line", [192, 448, 512, 1024, 2048])
+def test_panel_forms(lib, line, n_c):
+    n_c += line
+    print(f"case: N_c = {n_c}, panel line {line}", flush=True)
+    kw = contour(n_c)
+    with lib.Context(U=1.0, E=1.5, n_eps=1, n_ebar=2, **kw) as ctx:
+        assert ctx.n_c == n_c
+        sig = inputs.random_sigma(n_c, seed=n_c, scale=0.1)
+        go, jo = lattice(kw, sig, 1, 2)
+        ctx.set_sigma(sig)
+        ctx.compute_gloc()
+        assert relerr(ctx.get_gloc(), go) < 1e-10
+        assert relerr(ctx.get_current()[1], jo) < 1e-10
+        ctx.set_refinement(1)
+        ctx.compute_gloc(lib.FK_MIXED)
+        assert relerr(ctx.get_gloc(), go) < 1e-8
+
+
+def test_equal_pivot_candidates(lib):
+    """Sigma = 0 leaves columns whose candidates have equal magnitude: the
+    lowest row wins, in every run the same."""
+    print("case: equal pivot candidates, Sigma = 0", flush=True)
+    kw = contour(259)
+    with lib.Context(U=1.0, E=0.0, n_eps=3, n_ebar=3, **kw) as ctx:
+        first = None
+        for _ in range(2):
+            ctx.set_sigma(np.zeros((259, 259), complex))
+            ctx.compute_gloc()
+            g = ctx.get_gloc()
+            first = g if first is None else first
+        assert np.array_equal(first, g)
+    p = dmft.Problem(u=1.0, e_field=0.0, n_eps=3, n_ebar=3, **kw)
+    go = dmft.lattice_only(p, np.zeros((259, 259), complex))[0]
+    assert relerr(g, go) < 1e-10
