@@ -33,69 +33,285 @@ __device__ inline short f2bf(float x) {  // round to nearest even
   return (short)(u >> 16);
 }
 
-// C[M x N] = epi(op(A)[M x K] op(B)[K x N]) (+ beta C).  TA = 0: A[m][k] at
+// ------------------------------------------------ fused BF16 evaluation
+// The whole network on 128 rows per workgroup: the activations stay in LDS as
+// bf16 (a layer-by-layer evaluation moves 2 KB of FP32 activations per row and
+// layer through memory), a layer's outputs replace its inputs once every wave
+// has read them.  Eight waves, each 16 NT of the 128 NT columns of a hidden
+// layer for all rows.  The products are formed transposed (weights as the left
+// operand), so a lane ends up with four neighbouring columns of one row.  The
+// depths are summed in the order of the layer-by-layer products and with the
+// same roundings: the results are bit-identical to theirs.
+// Weights packed by k_pack_bf16: per layer and 16-column tile, for every 32
+// depths 64 lanes x 8 values (two k-steps of the lane's operand).
+constexpr int kFusedRows = 128, kFusedMax = 576;   // rows per block, widest layer
+__host__ __device__ inline size_t packed_layer(int o, int in) {
+  return (size_t)((o + 15) / 16) * ((in + 31) / 32) * 512;
+}
+__global__ void k_pack_bf16(const float* __restrict__ p, int d_in, int width, int depth,
+                            int d_out, short* __restrict__ wp) {
+  const int l = blockIdx.y;
+  size_t src = 0, dst = 0;
+  int in = d_in, o = width;
+  for (int q = 0; q < l; ++q) {
+    src += (size_t)o * in + o;
+    dst += packed_layer(o, in);
+    in = width;
+    o = q + 1 == depth - 1 ? d_out : width;
+  }
+  const int kp = (in + 31) / 32;
+  const int total = (int)packed_layer(o, in);
+  for (int e = blockIdx.x * blockDim.x + threadIdx.x; e < total; e += gridDim.x * blockDim.x) {
+    const int j = e & 7, lane = (e >> 3) & 63, t = e >> 9;
+    const int n = 16 * (t / kp) + (lane & 15);
+    const int k = 32 * (t % kp) + 16 * (j >> 2) + 4 * (lane >> 4) + (j & 3);
+    wp[dst + e] = (n < o && k < in) ? f2bf(p[src + (size_t)n * in + k]) : (short)0;
+  }
+}
+
+template <int NT>
+__global__ __launch_bounds__(512, 2) void k_mlp_bf16(
+    const float* __restrict__ x, int rows, int d_in, int depth, int d_out,
+    const float* __restrict__ p, const short* __restrict__ wp, float* __restrict__ y) {
+  typedef short v8s __attribute__((ext_vector_type(8)));
+  constexpr int W = 128 * NT, RT = kFusedRows / 16;
+  extern __shared__ __align__(16) short h[];         // [kFusedRows][pitch]
+  const int pitch = max(W, (d_in + 31) / 32 * 32) + 8;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int li = lane & 15, lk = lane >> 4;
+  const int r0 = blockIdx.x * kFusedRows;
+  const int kin = (d_in + 31) / 32 * 32;
+  for (int e = tid; e < kFusedRows * kin; e += 512) {
+    const int r = e / kin, k = e - r * kin;
+    const float v = k < d_in ? x[(size_t)min(r0 + r, rows - 1) * d_in + k] : 0.f;
+    h[r * pitch + k] = f2bf(v);
+  }
+  __syncthreads();
+  int in = d_in;
+  for (int l = 0; l + 1 < depth; ++l) {
+    const int kp = (in + 31) / 32;
+    const short* wt = wp + ((size_t)wave * NT * kp * 64 + lane) * 8;
+    v4f acc[NT][RT];
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+      for (int r = 0; r < RT; ++r) acc[t][r] = v4f{0.f, 0.f, 0.f, 0.f};
+    v8s w[NT], wn[NT];
+#pragma unroll
+    for (int t = 0; t < NT; ++t) w[t] = *reinterpret_cast<const v8s*>(wt + (size_t)t * kp * 512);
+    for (int q = 0; q < kp; ++q) {
+      const int qn = min(q + 1, kp - 1);
+#pragma unroll
+      for (int t = 0; t < NT; ++t)
+        wn[t] = *reinterpret_cast<const v8s*>(wt + ((size_t)t * kp + qn) * 512);
+#pragma unroll
+      for (int s = 0; s < 2; ++s) {
+#pragma unroll
+        for (int r = 0; r < RT; ++r) {
+          const v4s hv = *reinterpret_cast<const v4s*>(h + (16 * r + li) * pitch + 32 * q +
+                                                       16 * s + 4 * lk);
+#pragma unroll
+          for (int t = 0; t < NT; ++t) {
+            const v4s wv = s ? __builtin_shufflevector(w[t], w[t], 4, 5, 6, 7)
+                             : __builtin_shufflevector(w[t], w[t], 0, 1, 2, 3);
+            acc[t][r] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(wv, hv, acc[t][r], 0, 0, 0);
+          }
+        }
+      }
+#pragma unroll
+      for (int t = 0; t < NT; ++t) w[t] = wn[t];
+    }
+    __syncthreads();                                 // inputs read by every wave
+    const float* bias = p + (size_t)W * in;
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+      const int n = 16 * (wave * NT + t) + 4 * lk;
+      float b[4];
+#pragma unroll
+      for (int v = 0; v < 4; ++v) b[v] = bias[n + v];
+#pragma unroll
+      for (int r = 0; r < RT; ++r) {
+        v4s o;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) o[v] = f2bf(tanhf(acc[t][r][v] + b[v]));
+        *reinterpret_cast<v4s*>(h + (16 * r + li) * pitch + n) = o;
+      }
+    }
+    __syncthreads();
+    p = bias + W;
+    wp += packed_layer(W, in);
+    in = W;
+  }
+  // last layer: at most 16 outputs; each wave its 16 rows
+  const int kp = (in + 31) / 32;
+  v4f acc = v4f{0.f, 0.f, 0.f, 0.f};
+  for (int q = 0; q < kp; ++q) {
+    const v8s w = *reinterpret_cast<const v8s*>(wp + ((size_t)q * 64 + lane) * 8);
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+      const v4s hv = *reinterpret_cast<const v4s*>(h + (16 * wave + li) * pitch + 32 * q +
+                                                   16 * s + 4 * lk);
+      const v4s wv = s ? __builtin_shufflevector(w, w, 4, 5, 6, 7)
+                       : __builtin_shufflevector(w, w, 0, 1, 2, 3);
+      acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(wv, hv, acc, 0, 0, 0);
+    }
+  }
+  const int row = r0 + 16 * wave + li;
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    const int n = 4 * lk + v;
+    if (n < d_out && row < rows) y[(size_t)row * d_out + n] = acc[v] + p[(size_t)d_out * in + n];
+  }
+}
+
+// One operand's 64 x 32 chunk of a product: element (i, k) of the tile at rows
+// (or columns) i0 + i and depth k0 + k, from p[i ld + k] (KC, depth contiguous)
+// or p[k ld + i].  Eight values per thread in two quads along the contiguous
+// direction; `vec`: quads may be loaded whole (aligned base and ld).
+template <bool KC> struct Chunk {
+  float v[2][4];
+  __device__ __forceinline__ void load(const float* __restrict__ p, int ld, int i0, int ni,
+                                       int k0, int nk, bool vec) {
+    const int tid = threadIdx.x;
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      const int i = KC ? i0 + tid / 8 + 32 * q : i0 + 4 * (tid % 16);
+      const int k = KC ? k0 + 4 * (tid % 8) : k0 + tid / 16 + 16 * q;
+      const int lim = KC ? nk - k : ni - i;       // valid entries of the quad
+      const bool in = KC ? i < ni : k < nk;
+      const float* src = KC ? p + (size_t)i * ld + k : p + (size_t)k * ld + i;
+      if (in && vec && lim >= 4) {
+        *reinterpret_cast<float4*>(v[q]) = *reinterpret_cast<const float4*>(src);
+      } else {
+#pragma unroll
+        for (int t = 0; t < 4; ++t) v[q][t] = (in && t < lim) ? src[t] : 0.f;
+      }
+    }
+  }
+  // into s[i][k], rows of P floats
+  template <int P> __device__ __forceinline__ void store(float* s) const {
+    const int tid = threadIdx.x;
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      if (KC) {
+        *reinterpret_cast<float4*>(s + (tid / 8 + 32 * q) * P + 4 * (tid % 8)) =
+            *reinterpret_cast<const float4*>(v[q]);
+      } else {
+#pragma unroll
+        for (int t = 0; t < 4; ++t) s[(4 * (tid % 16) + t) * P + tid / 16 + 16 * q] = v[q][t];
+      }
+    }
+  }
+};
+
+// C[M x N] = epi(op(A)[M x K] op(B)[K x N]) in FP32.  TA = 0: A[m][k] at
 // A[m lda + k], TA = 1: at A[k lda + m]; TB = 0: B[k][n] at B[k ldb + n],
-// TB = 1: at B[n ldb + k].  EPI 0: plain, 1: + bias[n] then tanh, 2: + bias[n].
+// TB = 1: at B[n ldb + k].  EPI 0: plain, 1: + aux[n] then tanh, 2: + aux[n],
+// 3: times 1 - aux[m ldc + n]^2 (tanh derivative from the activation).
 // BF = 1 rounds both operands to bf16 and uses the bf16 matrix cores.
-// 64 x 64 tiles, 2 x 2 waves of 32 x 32, K chunks of 16 through LDS.
-template <int TA, int TB, int EPI, int BF>
-__global__ __launch_bounds__(256, 2) void k_gemm32(
+// 64 x 64 tiles, 2 x 2 waves of 32 x 32, chunks of 32 along K double-buffered
+// through LDS (4096 x 512 x 512: 57 -> 33 us; chunks of 64: 36).  Both operands lie depth-contiguous in LDS and a lane takes four
+// depths at once (k-step s of a lane group uses depths 4 (l/16) + s of each 16,
+// the same ones for A and B), so four products need one LDS read per operand.
+// Split along K over `splits` workgroups per tile (SK): every split writes its
+// part at C + split part, summed in fixed order afterwards (k_sum_parts): the
+// weight gradient's 64 tiles alone would leave three quarters of the chip idle
+// through 4096 rows (536 -> 37 us at 512 x 512 outputs, with the
+// column sums, which took another 748 us in one workgroup).  The workgroups
+// beyond the tiles sum the columns of A (the bias gradient) over their split.
+template <int TA, int TB, int EPI, int BF, bool SK>
+__global__ __launch_bounds__(256) void k_gemm32(
     const float* __restrict__ A, int lda, const float* __restrict__ B, int ldb,
-    float* __restrict__ C, int ldc, const float* __restrict__ bias, int M,
-    int N, int K, float beta) {
-  constexpr int T = 64, KC = 16, AP = KC + 1, BP = T + 1;
-  __shared__ float As[T * AP];
-  __shared__ float Bs[KC * BP];
+    float* __restrict__ C, int ldc, const float* __restrict__ aux, int M, int N,
+    int K, int splits, size_t part) {
+  constexpr int T = 64, KC = 32, P = KC + 4;
+  __shared__ __align__(16) float As[2][T * P];
+  __shared__ __align__(16) float Bs[2][T * P];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int ntn = (N + T - 1) / T, tiles = ((M + T - 1) / T) * ntn;
+  int bx = blockIdx.x, ka = 0, kb = K;
+  if (SK) {
+    const int split = bx % splits;
+    const int per = ((K + splits - 1) / splits + KC - 1) / KC * KC;
+    bx /= splits;
+    ka = min(K, split * per);
+    kb = min(K, ka + per);
+    C += split * part;
+    if (bx >= tiles) {             // column sums of A over [ka, kb)
+      const int c = (bx - tiles) * T + (tid & 63), g = tid >> 6;
+      float sum = 0.f;
+      if (c < M)
+        for (int k = ka + g; k < kb; k += 4) sum += A[(size_t)k * lda + c];
+      As[0][tid] = sum;
+      __syncthreads();
+      if (g == 0 && c < M)
+        C[(size_t)M * N + c] = (As[0][lane] + As[0][64 + lane]) + (As[0][128 + lane] + As[0][192 + lane]);
+      return;
+    }
+  }
   const int wr = wave >> 1, wc = wave & 1, li = lane & 15, lk = lane >> 4;
-  const int ntn = (N + T - 1) / T;
-  const int r0 = (blockIdx.x / ntn) * T, c0 = (blockIdx.x % ntn) * T;
+  const int r0 = (bx / ntn) * T, c0 = (bx % ntn) * T;
+  const bool va = (lda % 4) == 0 && (reinterpret_cast<size_t>(A) & 15) == 0;
+  const bool vb = (ldb % 4) == 0 && (reinterpret_cast<size_t>(B) & 15) == 0;
   v4f acc[2][2];
 #pragma unroll
   for (int ii = 0; ii < 2; ++ii)
 #pragma unroll
     for (int jj = 0; jj < 2; ++jj) acc[ii][jj] = v4f{0.f, 0.f, 0.f, 0.f};
-  for (int k0 = 0; k0 < K; k0 += KC) {
+  Chunk<TA == 0> pa;
+  Chunk<TB == 1> pb;
+  if (ka < kb) {
+    pa.load(A, lda, r0, M, ka, kb, va);
+    pb.load(B, ldb, c0, N, ka, kb, vb);
+    pa.template store<P>(As[0]);
+    pb.template store<P>(Bs[0]);
     __syncthreads();
+    int buf = 0;
+    for (int k0 = ka; k0 < kb; k0 += KC, buf ^= 1) {
+      const bool more = k0 + KC < kb;
+      if (more) {
+        pa.load(A, lda, r0, M, k0 + KC, kb, va);
+        pb.load(B, ldb, c0, N, k0 + KC, kb, vb);
+      }
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int e = tid + q * 256;
-      const int i = e / KC, k = e % KC;                 // A: 64 rows x 16 k
-      const int m = r0 + i, kk = k0 + k;
-      float a = 0.f;
-      if (m < M && kk < K) a = TA ? A[(size_t)kk * lda + m] : A[(size_t)m * lda + kk];
-      As[i * AP + k] = a;
-      const int k2 = e / T, c = e % T;                  // B: 16 k x 64 cols
-      const int n = c0 + c, kb = k0 + k2;
-      float b = 0.f;
-      if (n < N && kb < K) b = TB ? B[(size_t)n * ldb + kb] : B[(size_t)kb * ldb + n];
-      Bs[k2 * BP + c] = b;
-    }
-    __syncthreads();
-    if (BF) {
-#pragma unroll
-      for (int ii = 0; ii < 2; ++ii)
-#pragma unroll
-        for (int jj = 0; jj < 2; ++jj) {
-          v4s av, bv;
-#pragma unroll
-          for (int t = 0; t < 4; ++t) {
-            av[t] = f2bf(As[(32 * wr + 16 * ii + li) * AP + 4 * lk + t]);
-            bv[t] = f2bf(Bs[(4 * lk + t) * BP + 32 * wc + 16 * jj + li]);
-          }
-          acc[ii][jj] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(av, bv, acc[ii][jj], 0, 0, 0);
-        }
-    } else {
-#pragma unroll
-      for (int k = 0; k < KC; k += 4)
+      for (int k = 0; k < KC; k += 16) {
+        v4f a[2], b[2];
 #pragma unroll
         for (int ii = 0; ii < 2; ++ii)
+          a[ii] = *reinterpret_cast<const v4f*>(As[buf] + (32 * wr + 16 * ii + li) * P + k + 4 * lk);
 #pragma unroll
-          for (int jj = 0; jj < 2; ++jj) {
-            const float a = As[(32 * wr + 16 * ii + li) * AP + k + lk];
-            const float b = Bs[(k + lk) * BP + 32 * wc + 16 * jj + li];
-            acc[ii][jj] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, acc[ii][jj], 0, 0, 0);
-          }
+        for (int jj = 0; jj < 2; ++jj)
+          b[jj] = *reinterpret_cast<const v4f*>(Bs[buf] + (32 * wc + 16 * jj + li) * P + k + 4 * lk);
+        if (BF) {
+          v4s av[2], bv[2];
+#pragma unroll
+          for (int q = 0; q < 2; ++q)
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+              av[q][t] = f2bf(a[q][t]);
+              bv[q][t] = f2bf(b[q][t]);
+            }
+#pragma unroll
+          for (int ii = 0; ii < 2; ++ii)
+#pragma unroll
+            for (int jj = 0; jj < 2; ++jj)
+              acc[ii][jj] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(av[ii], bv[jj], acc[ii][jj], 0, 0, 0);
+        } else {
+#pragma unroll
+          for (int s = 0; s < 4; ++s)
+#pragma unroll
+            for (int ii = 0; ii < 2; ++ii)
+#pragma unroll
+              for (int jj = 0; jj < 2; ++jj)
+                acc[ii][jj] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[ii][s], b[jj][s], acc[ii][jj], 0, 0, 0);
+        }
+      }
+      if (more) {
+        pa.template store<P>(As[buf ^ 1]);
+        pb.template store<P>(Bs[buf ^ 1]);
+      }
+      __syncthreads();
     }
   }
 #pragma unroll
@@ -108,9 +324,12 @@ __global__ __launch_bounds__(256, 2) void k_gemm32(
         const int n = c0 + 32 * wc + 16 * jj + li;
         if (m < M && n < N) {
           float y = acc[ii][jj][v];
-          if (EPI >= 1) y += bias[n];
+          if (EPI == 1 || EPI == 2) y += aux[n];
           if (EPI == 1) y = tanhf(y);
-          if (beta != 0.f) y += beta * C[(size_t)m * ldc + n];
+          if (EPI == 3) {
+            const float h = aux[(size_t)m * ldc + n];
+            y *= 1.f - h * h;
+          }
           C[(size_t)m * ldc + n] = y;
         }
       }
@@ -118,20 +337,51 @@ __global__ __launch_bounds__(256, 2) void k_gemm32(
 
 template <int TA, int TB, int EPI, int BF>
 hipError_t gemm32(const float* A, int lda, const float* B, int ldb, float* C,
-                  int ldc, const float* bias, int M, int N, int K, float beta,
-                  hipStream_t st) {
+                  int ldc, const float* aux, int M, int N, int K, hipStream_t st) {
   const int tiles = ((M + 63) / 64) * ((N + 63) / 64);
-  hipLaunchKernelGGL((k_gemm32<TA, TB, EPI, BF>), dim3(tiles), dim3(256), 0, st,
-                     A, lda, B, ldb, C, ldc, bias, M, N, K, beta);
+  hipLaunchKernelGGL((k_gemm32<TA, TB, EPI, BF, false>), dim3(tiles), dim3(256), 0, st,
+                     A, lda, B, ldb, C, ldc, aux, M, N, K, 1, 0);
   return hipGetLastError();
 }
 
-// dZ = dH * (1 - H^2) (tanh derivative), in place
-__global__ void k_tanh_back(float* __restrict__ d, const float* __restrict__ h,
-                            size_t n) {
-  for (size_t e = blockIdx.x * (size_t)blockDim.x + threadIdx.x; e < n;
-       e += (size_t)gridDim.x * blockDim.x)
-    d[e] *= 1.f - h[e] * h[e];
+// Gradient parts of one layer: dW = d^T h (o x in) and db = column sums of d,
+// over `splits` parts of the rows; part s of both at parts + s (o in + o).
+hipError_t gemm32_grad(const float* d, int o, const float* h, int in, float* parts,
+                       int rows, int splits, hipStream_t st) {
+  const int tiles = ((o + 63) / 64) * ((in + 63) / 64) + (o + 63) / 64;
+  hipLaunchKernelGGL((k_gemm32<1, 0, 0, 0, true>), dim3(tiles * splits), dim3(256), 0, st, d, o,
+                     h, in, parts, in, nullptr, o, in, rows, splits,
+                     (size_t)o * in + o);
+  return hipGetLastError();
+}
+// Parts per tile: about four workgroups per CU, 128 rows at least.
+int grad_splits(int o, int in, int rows) {
+  const int tiles = ((o + 63) / 64) * ((in + 63) / 64);
+  return std::max(1, std::min(std::min(32, (rows + 127) / 128), 1024 / tiles));
+}
+
+// g[e] = sum over the layer's parts of parts[s np + e], ascending s; one layer
+// per blockIdx.y.  Block (0, 0) also sums the squared residuals' partial sums.
+constexpr int kPartLayers = 16;
+struct PartList {
+  const float* parts[kPartLayers];
+  float* g[kPartLayers];
+  int n[kPartLayers];
+  int splits[kPartLayers];
+};
+__global__ void k_sum_parts(PartList pl, const double* __restrict__ partial, int npart,
+                            int rows, double* __restrict__ loss) {
+  const int l = blockIdx.y, n = pl.n[l], splits = pl.splits[l];
+  for (int e = blockIdx.x * blockDim.x + threadIdx.x; e < n; e += gridDim.x * blockDim.x) {
+    float s = 0.f;
+    for (int q = 0; q < splits; ++q) s += pl.parts[l][(size_t)q * n + e];
+    pl.g[l][e] = s;
+  }
+  if (loss && l == 0 && blockIdx.x == 0 && threadIdx.x == 0) {
+    double s = 0.0;
+    for (int q = 0; q < npart; ++q) s += partial[q];
+    *loss = s / rows;
+  }
 }
 
 // dY = 2 (Y - T) / rows; per-block partial sums of (Y - T)^2
@@ -153,16 +403,6 @@ __global__ void k_mse(const float* __restrict__ y, const float* __restrict__ t,
     __syncthreads();
   }
   if (threadIdx.x == 0) partial[blockIdx.x] = red[0];
-}
-
-// db[n] = sum over rows of dZ[r][n]
-__global__ void k_colsum(const float* __restrict__ d, int rows, int cols,
-                         float* __restrict__ out) {
-  const int c = blockIdx.x * blockDim.x + threadIdx.x;
-  if (c >= cols) return;
-  float s = 0.f;
-  for (int r = 0; r < rows; ++r) s += d[(size_t)r * cols + c];
-  out[c] = s;
 }
 
 __global__ void k_adam(float* __restrict__ p, const float* __restrict__ g,
@@ -365,10 +605,13 @@ struct fk_mlp {
   float* d1 = nullptr;
   float* xs = nullptr;   // gathered minibatch
   float* ts = nullptr;
-  double* partial = nullptr;
+  double* partial = nullptr;   // k_mse's partial sums, then the loss
+  std::vector<float*> parts;   // gradient parts per layer
+  short* wp = nullptr;         // weights packed for k_mlp_bf16
   hipStream_t st = nullptr;
   std::string err;
 };
+static constexpr int kMsePartials = 1024;
 
 namespace {
 fk_status merr(fk_mlp* a, fk_status s, const char* fmt, ...) {
@@ -400,6 +643,9 @@ void free_work(fk_mlp* a) {
   if (a->partial) (void)hipFree(a->partial);
   if (a->xs) (void)hipFree(a->xs);
   if (a->ts) (void)hipFree(a->ts);
+  for (float* q : a->parts)
+    if (q) (void)hipFree(q);
+  a->parts.clear();
   a->xs = a->ts = nullptr;
   a->d0 = a->d1 = nullptr;
   a->partial = nullptr;
@@ -415,9 +661,15 @@ fk_status ensure_work(fk_mlp* a, int rows) {
   const size_t dw = (size_t)std::max(a->width, a->d_out);
   MCHK(a, hipMalloc(&a->d0, sizeof(float) * (size_t)rows * dw));
   MCHK(a, hipMalloc(&a->d1, sizeof(float) * (size_t)rows * dw));
-  MCHK(a, hipMalloc(&a->partial, sizeof(double) * 1024));
+  MCHK(a, hipMalloc(&a->partial, sizeof(double) * (kMsePartials + 1)));
   MCHK(a, hipMalloc(&a->xs, sizeof(float) * (size_t)rows * a->d_in));
   MCHK(a, hipMalloc(&a->ts, sizeof(float) * (size_t)rows * a->d_out));
+  a->parts.assign(a->depth, nullptr);
+  for (int l = 0; l < a->depth; ++l) {
+    const int o = a->shapes[l].first, in = a->shapes[l].second;
+    MCHK(a, hipMalloc(&a->parts[l], sizeof(float) * ((size_t)o * in + o) *
+                                        grad_splits(o, in, rows)));
+  }
   a->cap = rows;
   return FK_OK;
 }
@@ -433,26 +685,51 @@ hipError_t forward(fk_mlp* a, const float* x, int rows, bool bf16, float* out) {
     float* y = (l == a->depth - 1 && out) ? out : a->h[l + 1];
     const bool last = l == a->depth - 1;
     if (bf16)
-      e = last ? gemm32<0, 1, 2, 1>(a->h[l], in, W, in, y, o, b, rows, o, in, 0.f, a->st)
-               : gemm32<0, 1, 1, 1>(a->h[l], in, W, in, y, o, b, rows, o, in, 0.f, a->st);
+      e = last ? gemm32<0, 1, 2, 1>(a->h[l], in, W, in, y, o, b, rows, o, in, a->st)
+               : gemm32<0, 1, 1, 1>(a->h[l], in, W, in, y, o, b, rows, o, in, a->st);
     else
-      e = last ? gemm32<0, 1, 2, 0>(a->h[l], in, W, in, y, o, b, rows, o, in, 0.f, a->st)
-               : gemm32<0, 1, 1, 0>(a->h[l], in, W, in, y, o, b, rows, o, in, 0.f, a->st);
+      e = last ? gemm32<0, 1, 2, 0>(a->h[l], in, W, in, y, o, b, rows, o, in, a->st)
+               : gemm32<0, 1, 1, 0>(a->h[l], in, W, in, y, o, b, rows, o, in, a->st);
     if (e != hipSuccess) return e;
   }
   return e;
 }
 
-// loss and gradient of a batch into a->g; returns the loss in *loss
+template <int NT>
+hipError_t launch_fused(fk_mlp* a, const float* x, int rows, float* y) {
+  const int pitch = std::max(128 * NT, (a->d_in + 31) / 32 * 32) + 8;
+  const size_t lds = sizeof(short) * (size_t)kFusedRows * pitch;
+  // the limit of dynamic LDS is the device's attribute of each kernel
+  const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_mlp_bf16<NT>),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize,
+                                           (int)lds);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(k_mlp_bf16<NT>, dim3((rows + kFusedRows - 1) / kFusedRows), dim3(512),
+                     lds, a->st, x, rows, a->d_in, a->depth, a->d_out, a->p, a->wp, y);
+  return hipGetLastError();
+}
+// the weights are packed on every call: the parameters may have changed
+hipError_t forward_fused(fk_mlp* a, const float* x, int rows, float* y) {
+  hipLaunchKernelGGL(k_pack_bf16, dim3(64, a->depth), dim3(256), 0, a->st, a->p, a->d_in,
+                     a->width, a->depth, a->d_out, a->wp);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  switch (a->width / 128) {
+    case 1: return launch_fused<1>(a, x, rows, y);
+    case 2: return launch_fused<2>(a, x, rows, y);
+    case 3: return launch_fused<3>(a, x, rows, y);
+    default: return launch_fused<4>(a, x, rows, y);
+  }
+}
+
+// loss and gradient of a batch into a->g; the loss to *loss_dev (device)
 fk_status loss_grad(fk_mlp* a, const float* x, const float* t, int rows,
-                    double* loss) {
-  fk_status s = ensure_work(a, rows);
-  if (s != FK_OK) return s;
+                    double* loss_dev) {
   MCHK(a, forward(a, x, rows, false, nullptr));
   const int L = a->depth;
   const int dout = a->shapes[L - 1].first;
   const size_t ny = (size_t)rows * dout;
-  int gb = (int)std::min<size_t>((ny + 255) / 256, 1024);
+  int gb = (int)std::min<size_t>((ny + 255) / 256, kMsePartials);
   hipLaunchKernelGGL(k_mse, dim3(gb), dim3(256), 0, a->st, a->h[L], t, a->d0, ny,
                      1.f / rows, a->partial);
   MCHK(a, hipGetLastError());
@@ -460,32 +737,29 @@ fk_status loss_grad(fk_mlp* a, const float* x, const float* t, int rows,
   float* dn = a->d1;
   for (int l = L - 1; l >= 0; --l) {
     const int o = a->shapes[l].first, in = a->shapes[l].second;
-    if (l < L - 1) {
-      const size_t n = (size_t)rows * o;
-      hipLaunchKernelGGL(k_tanh_back, dim3((int)std::min<size_t>((n + 255) / 256, 4096)),
-                         dim3(256), 0, a->st, d, a->h[l + 1], n);
-      MCHK(a, hipGetLastError());
-    }
-    // dW = d^T h_l  (o x in), db = column sums of d
-    MCHK(a, (gemm32<1, 0, 0, 0>(d, o, a->h[l], in, a->g + a->woff[l], in, nullptr,
-                                o, in, rows, 0.f, a->st)));
-    hipLaunchKernelGGL(k_colsum, dim3((o + 255) / 256), dim3(256), 0, a->st, d, rows,
-                       o, a->g + a->boff[l]);
-    MCHK(a, hipGetLastError());
-    if (l > 0) {   // d_{l-1} = d W_l  (rows x in)
-      MCHK(a, (gemm32<0, 0, 0, 0>(d, o, a->p + a->woff[l], in, dn, in, nullptr, rows,
-                                  in, o, 0.f, a->st)));
+    MCHK(a, gemm32_grad(d, o, a->h[l], in, a->parts[l], rows, grad_splits(o, in, rows),
+                        a->st));
+    if (l > 0) {   // d_{l-1} = d W_l (1 - h_l^2)  (rows x in)
+      MCHK(a, (gemm32<0, 0, 3, 0>(d, o, a->p + a->woff[l], in, dn, in, a->h[l], rows, in, o,
+                               a->st)));
       std::swap(d, dn);
     }
   }
-  if (loss) {
-    std::vector<double> part(gb);
-    MCHK(a, hipMemcpyAsync(part.data(), a->partial, sizeof(double) * gb,
-                           hipMemcpyDeviceToHost, a->st));
-    MCHK(a, hipStreamSynchronize(a->st));
-    double sum = 0.0;
-    for (double q : part) sum += q;
-    *loss = sum / rows;
+  for (int l0 = 0; l0 < L; l0 += kPartLayers) {
+    PartList pl{};
+    int most = 0;
+    const int nl = std::min(kPartLayers, L - l0);
+    for (int l = 0; l < nl; ++l) {
+      const int o = a->shapes[l0 + l].first, in = a->shapes[l0 + l].second;
+      pl.parts[l] = a->parts[l0 + l];
+      pl.g[l] = a->g + a->woff[l0 + l];     // W_l and b_l are adjacent
+      pl.n[l] = o * in + o;
+      pl.splits[l] = grad_splits(o, in, rows);
+      most = std::max(most, pl.n[l]);
+    }
+    hipLaunchKernelGGL(k_sum_parts, dim3((most + 255) / 256, nl), dim3(256), 0, a->st, pl,
+                       a->partial, gb, rows, l0 == 0 ? loss_dev : nullptr);
+    MCHK(a, hipGetLastError());
   }
   return FK_OK;
 }
@@ -536,6 +810,7 @@ extern "C" fk_status fk_mlp_destroy(fk_mlp* a) {
   float* ps[] = {a->p, a->g, a->m, a->v};
   for (float* q : ps)
     if (q) (void)hipFree(q);
+  if (a->wp) (void)hipFree(a->wp);
   if (a->st) (void)hipStreamDestroy(a->st);
   delete a;
   return FK_OK;
@@ -572,6 +847,20 @@ extern "C" fk_status fk_mlp_set_params(fk_mlp* a, const float* params) {
 extern "C" fk_status fk_mlp_forward(fk_mlp* a, const float* x_dev, int rows,
                                     float* y_dev, int bf16) {
   if (!a || !x_dev || !y_dev || rows < 1) return FK_EINVAL;
+  // BF16: the fused kernel where a block's activations fit LDS and the waves
+  // share the columns evenly (the warm start's network among them: 360,000
+  // rows of 96 -> 512 x 3 -> 2 7.9 -> 1.0 ms); otherwise layer by layer
+  if (bf16 && a->width % 128 == 0 && a->width <= 512 && a->d_in <= kFusedMax &&
+      a->d_out <= 16) {
+    if (!a->wp) {
+      size_t n = 0;
+      for (const auto& sh : a->shapes) n += packed_layer(sh.first, sh.second);
+      MCHK(a, hipMalloc(&a->wp, sizeof(short) * n));
+    }
+    MCHK(a, forward_fused(a, x_dev, rows, y_dev));
+    MCHK(a, hipStreamSynchronize(a->st));
+    return FK_OK;
+  }
   // evaluate in slices of at most 65536 rows to bound the work buffers
   const int slice = 65536;
   fk_status s = ensure_work(a, std::min(rows, slice));
@@ -589,15 +878,27 @@ extern "C" fk_status fk_mlp_loss_grad(fk_mlp* a, const float* x_dev,
                                       const float* t_dev, int rows, double* loss,
                                       float* grad_host) {
   if (!a || !x_dev || !t_dev || rows < 1) return FK_EINVAL;
-  fk_status s = loss_grad(a, x_dev, t_dev, rows, loss);
+  fk_status s = ensure_work(a, rows);
   if (s != FK_OK) return s;
-  if (grad_host) {
+  double* ld = a->partial + kMsePartials;
+  if ((s = loss_grad(a, x_dev, t_dev, rows, ld)) != FK_OK) return s;
+  if (grad_host)
     MCHK(a, hipMemcpyAsync(grad_host, a->g, sizeof(float) * a->np, hipMemcpyDeviceToHost,
                            a->st));
-  }
+  if (loss)
+    MCHK(a, hipMemcpyAsync(loss, ld, sizeof(double), hipMemcpyDeviceToHost, a->st));
   MCHK(a, hipStreamSynchronize(a->st));
   return FK_OK;
 }
+
+namespace {
+struct CallLosses {   // freed once the stream is done with it
+  double* p = nullptr;
+  ~CallLosses() {
+    if (p) (void)hipFree(p);
+  }
+};
+}  // namespace
 
 // Adam steps on minibatches sampled with replacement (see the header).
 extern "C" fk_status fk_mlp_train(fk_mlp* a, const float* x_dev, const float* t_dev,
@@ -607,15 +908,16 @@ extern "C" fk_status fk_mlp_train(fk_mlp* a, const float* x_dev, const float* t_
     return FK_EINVAL;
   fk_status st = ensure_work(a, batch);
   if (st != FK_OK) return st;
+  // the steps' losses are kept on the device and read once
+  CallLosses ls;
+  if (loss_hist) MCHK(a, hipMalloc(&ls.p, sizeof(double) * (size_t)steps));
   for (int s = 0; s < steps; ++s) {
     hipLaunchKernelGGL(k_gather_rows, dim3(batch), dim3(64), 0, a->st, x_dev, t_dev,
                        (long long)rows, a->d_in, a->d_out, batch, seed, (long long)s,
                        a->xs, a->ts);
     MCHK(a, hipGetLastError());
-    double loss = 0.0;
-    st = loss_grad(a, a->xs, a->ts, batch, loss_hist ? &loss : nullptr);
+    st = loss_grad(a, a->xs, a->ts, batch, loss_hist ? ls.p + s : nullptr);
     if (st != FK_OK) return st;
-    if (loss_hist) loss_hist[s] = loss;
     a->step++;
     const float b1 = 0.9f, b2 = 0.999f;
     const float c1 = 1.f - powf(b1, (float)a->step), c2 = 1.f - powf(b2, (float)a->step);
@@ -624,6 +926,9 @@ extern "C" fk_status fk_mlp_train(fk_mlp* a, const float* x_dev, const float* t_
                        1e-8f, c1, c2);
     MCHK(a, hipGetLastError());
   }
+  if (loss_hist)
+    MCHK(a, hipMemcpyAsync(loss_hist, ls.p, sizeof(double) * (size_t)steps,
+                           hipMemcpyDeviceToHost, a->st));
   MCHK(a, hipStreamSynchronize(a->st));
   return FK_OK;
 }

@@ -198,3 +198,45 @@ def test_judged_loop_accepts_rejects_and_falls_back(lib):
         c.set_sigma(prev)
         r = c.iterate_judged(prev, 200, tol=tol)
         assert r["outcome"] == 0 and r["iters"] == plain["iters"]
+
+
+@pytest.mark.parametrize("d_in,width,depth,d_out,rows", [
+    (96, 512, 4, 2, 127), (96, 512, 4, 2, 129),   # edges of a block of 128 rows
+    (33, 128, 2, 16, 300), (64, 256, 3, 1, 128),  # widths of one to three tiles
+    (20, 384, 2, 5, 1),
+    (576, 128, 2, 2, 140), (577, 128, 2, 2, 140),  # widest input in one block, and beyond
+    (64, 256, 2, 17, 140), (64, 640, 2, 2, 65),    # layer by layer
+])
+def test_bf16_forward_shapes(lib, d_in, width, depth, d_out, rows):
+    say(f"case: BF16 forward, {d_in} -> {width} x {depth - 1} -> {d_out}, rows {rows}")
+    shapes = omlp.layer_shapes(d_in, width, depth, d_out)
+    p = inputs.network_params(shapes, seed=14)
+    x = inputs.random_rows(rows, d_in, seed=15)
+    net = lib.MLP(d_in, width, depth, d_out, params=p)
+    y = net.forward(dev(x), bf16=True).cpu().numpy()
+    yo, _ = omlp.forward(p.astype(np.float64), shapes, x.astype(np.float64), bf16=True)
+    assert relerr(y, yo) < 3e-3
+    net.set_params(0.5 * p)                        # changed parameters are used
+    y = net.forward(dev(x), bf16=True).cpu().numpy()
+    yo, _ = omlp.forward(0.5 * p.astype(np.float64), shapes, x.astype(np.float64), bf16=True)
+    assert relerr(y, yo) < 3e-3
+    net.close()
+
+
+@pytest.mark.parametrize("d_in,width,depth,d_out,rows", [
+    (95, 70, 3, 3, 1), (96, 512, 4, 2, 257), (7, 65, 18, 2, 130), (64, 130, 2, 66, 1500)])
+def test_gradient_shapes(lib, d_in, width, depth, d_out, rows):
+    """Split row sums: one part and many, odd leading dimensions, more layers
+    than one summation launch takes."""
+    say(f"case: gradient, {d_in} -> {width} x {depth - 1} -> {d_out}, rows {rows}")
+    shapes = omlp.layer_shapes(d_in, width, depth, d_out)
+    p = inputs.network_params(shapes, seed=16)
+    x = inputs.random_rows(rows, d_in, seed=17)
+    t = inputs.random_rows(rows, d_out, seed=18)
+    net = lib.MLP(d_in, width, depth, d_out, params=p)
+    loss, g = net.loss_grad(dev(x), dev(t))
+    lo, go = omlp.loss_and_grad(p.astype(np.float64), shapes, x.astype(np.float64),
+                                t.astype(np.float64))
+    assert abs(loss - lo) < 1e-5 * lo
+    assert relerr(g, go) < 1e-4
+    net.close()
