@@ -11,6 +11,8 @@
 #include "fk_internal.h"
 #include "fk_kernels.h"
 
+#include <algorithm>
+
 namespace fk {
 
 // ------------------------------------------------------------ Sigma_t ------
@@ -119,63 +121,102 @@ __global__ void k_build(const c64* __restrict__ sigt,
 }
 
 // ------------------------------------------------------------- reduce ------
-// out[a][b] += sum_m coef[m] X_m[piv_m[a]][rowcol_m[b]]   (m in fixed order)
+// out[a][b] (+)= sum_m coef[m] X_m[piv_m[a]][rowcol_m[b]], in fixed order: four
+// groups of threads take the matrices m = g, g + 4, ... of a row's 64 columns,
+// four at a time so that the loads (permutation, then entry) of four matrices
+// are in flight, and the groups' sums are added in order.  Streams the batch
+// once at the rate of a copy (225 matrices of N_c = 1800: 4.9 TB/s, as one
+// thread per column did); for small matrices the chain of one thread through
+// the batch took the time (100 of N_c = 150: 57 -> 10 us).
+constexpr int kRedCols = 64, kRedGroups = 4, kRedAhead = 4;
 template <typename TI>
-__global__ void k_reduce(const cplx<TI>* __restrict__ xbuf, size_t mat_stride,
-                         int ld, const int* __restrict__ pivbuf,
-                         const int* __restrict__ rowcolbuf, int istride,
-                         const double* __restrict__ coef, int nmat, int n,
-                         c64* __restrict__ out, int accumulate) {
-  const int a = blockIdx.y;
-  for (int b = blockIdx.x * blockDim.x + threadIdx.x; b < n;
-       b += gridDim.x * blockDim.x) {
-    double re = 0.0, im = 0.0;
-    for (int m = 0; m < nmat; ++m) {
-      const int r = pivbuf[(size_t)m * istride + a];
-      const int c = rowcolbuf[(size_t)m * istride + b];
-      if (r < 0 || c < 0 || r >= n || c >= n) {  // incomplete inversion
-        re = im = __builtin_nan("");
-        continue;
+__global__ __launch_bounds__(kRedCols * kRedGroups) void k_reduce(
+    const cplx<TI>* __restrict__ xbuf, size_t mat_stride, int ld,
+    const int* __restrict__ pivbuf, const int* __restrict__ rowcolbuf, int istride,
+    const double* __restrict__ coef, int nmat, int n, c64* __restrict__ out, int accumulate) {
+  __shared__ c64 part[kRedGroups][kRedCols];
+  const int a = blockIdx.y, lc = threadIdx.x % kRedCols, g = threadIdx.x / kRedCols;
+  const int b = blockIdx.x * kRedCols + lc;
+  double re = 0.0, im = 0.0;
+  if (b < n) {
+    for (int m0 = g; m0 < nmat; m0 += kRedGroups * kRedAhead) {
+      int r[kRedAhead], c[kRedAhead];
+      cplx<TI> v[kRedAhead];
+      double w[kRedAhead];
+#pragma unroll
+      for (int u = 0; u < kRedAhead; ++u) {
+        const int m = m0 + kRedGroups * u, mc = min(m, nmat - 1);
+        r[u] = pivbuf[(size_t)mc * istride + a];
+        c[u] = rowcolbuf[(size_t)mc * istride + b];
+        w[u] = coef[mc];
       }
-      const cplx<TI> v = xbuf[(size_t)m * mat_stride + (size_t)r * ld + c];
-      const double w = coef[m];
-      re += w * (double)v.re;
-      im += w * (double)v.im;
+#pragma unroll
+      for (int u = 0; u < kRedAhead; ++u) {
+        const int m = m0 + kRedGroups * u, mc = min(m, nmat - 1);
+        const bool ok = r[u] >= 0 && c[u] >= 0 && r[u] < n && c[u] < n;
+        v[u] = xbuf[(size_t)mc * mat_stride + (size_t)(ok ? r[u] : 0) * ld + (ok ? c[u] : 0)];
+        if (!ok) w[u] = __builtin_nan("");       // incomplete inversion
+      }
+#pragma unroll
+      for (int u = 0; u < kRedAhead; ++u)
+        if (m0 + kRedGroups * u < nmat) {
+          re += w[u] * (double)v[u].re;
+          im += w[u] * (double)v[u].im;
+        }
     }
+  }
+  part[g][lc] = c64{re, im};
+  __syncthreads();
+  if (g == 0 && b < n) {
     c64 o = accumulate ? out[(size_t)a * n + b] : c64{0.0, 0.0};
-    o.re += re;
-    o.im += im;
+#pragma unroll
+    for (int q = 0; q < kRedGroups; ++q) {
+      o.re += part[q][lc].re;
+      o.im += part[q][lc].im;
+    }
     out[(size_t)a * n + b] = o;
   }
 }
 
 // j(t_i) += sum_m rho_m vel_m(i) Re[i G_m[i][2 n_t - i]],
 // vel_m(i) = ebar cos(E t_i) + eps sin(E t_i) for t_i > 0, else ebar.
+// Each entry is one lone load behind two permutation loads, so 32 threads share
+// a time's sum over the matrices (fixed order); one thread per time took
+// 54 us for 100 matrices and 257 us for 225, now 7 and 18.
+constexpr int kCurTimes = 8, kCurGroups = 32;
 template <typename TI>
-__global__ void k_current(const cplx<TI>* __restrict__ xbuf, size_t mat_stride,
-                          int ld, const int* __restrict__ pivbuf,
-                          const int* __restrict__ rowcolbuf, int istride,
-                          const PointTables tab, int k0, int nmat, int n_t,
-                          int n, double* __restrict__ cur) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n_t) return;
-  const int pcol = 2 * n_t - i;
-  const double ct = tab.cos_et[i], st = tab.sin_et[i];
-  const bool on = tab.t_pos[i] != 0;
+__global__ __launch_bounds__(kCurTimes * kCurGroups) void k_current(
+    const cplx<TI>* __restrict__ xbuf, size_t mat_stride, int ld,
+    const int* __restrict__ pivbuf, const int* __restrict__ rowcolbuf, int istride,
+    const PointTables tab, int k0, int nmat, int n_t, int n, double* __restrict__ cur) {
+  __shared__ double part[kCurGroups][kCurTimes];
+  const int li = threadIdx.x % kCurTimes, g = threadIdx.x / kCurTimes;
+  const int i = blockIdx.x * kCurTimes + li;
   double acc = 0.0;
-  for (int m = 0; m < nmat; ++m) {
-    const int k = k0 + m;
-    const int r = pivbuf[(size_t)m * istride + i];
-    const int c = rowcolbuf[(size_t)m * istride + pcol];
-    if (r < 0 || c < 0 || r >= n || c >= n) {
-      acc = __builtin_nan("");
-      continue;
+  if (i < n_t) {
+    const int pcol = 2 * n_t - i;
+    const double ct = tab.cos_et[i], st = tab.sin_et[i];
+    const bool on = tab.t_pos[i] != 0;
+#pragma unroll 4
+    for (int m = g; m < nmat; m += kCurGroups) {
+      const int k = k0 + m;
+      const int r = pivbuf[(size_t)m * istride + i];
+      const int c = rowcolbuf[(size_t)m * istride + pcol];
+      const bool ok = r >= 0 && c >= 0 && r < n && c < n;
+      const cplx<TI> v = xbuf[(size_t)m * mat_stride + (size_t)(ok ? r : 0) * ld + (ok ? c : 0)];
+      const double vel = on ? tab.ebar[k] * ct + tab.eps[k] * st : tab.ebar[k];
+      const double t = tab.rho[k] * vel * (-(double)v.im);  // Re[i g] = -Im g
+      acc += ok ? t : __builtin_nan("");
     }
-    const cplx<TI> v = xbuf[(size_t)m * mat_stride + (size_t)r * ld + c];
-    const double vel = on ? tab.ebar[k] * ct + tab.eps[k] * st : tab.ebar[k];
-    acc += tab.rho[k] * vel * (-(double)v.im);  // Re[i g] = -Im g
   }
-  cur[i] += acc;
+  part[g][li] = acc;
+  __syncthreads();
+  if (g == 0 && i < n_t) {
+    double sum = 0.0;
+#pragma unroll
+    for (int q = 0; q < kCurGroups; ++q) sum += part[q][li];
+    cur[i] += sum;
+  }
 }
 
 // Equal-time entries of G_loc: less[i] = G[i][2 N_t - i] (G^<(t_i, t_i)) and
@@ -212,30 +253,69 @@ __device__ inline c64 retarded_pair(const c64* __restrict__ g, int n_t, int n,
 }
 
 // Nonequilibrium DOS (Sec. II, eqs. gr_omega and dos_def) at the average times
-// T = t_i, i = tix[r], and the frequencies w[q]: one thread per frequency and
-// time (times strided over the grid's y dimension),
+// T = t_i, i = tix[r], and the frequencies w[q]:
 //   rho = -(h / pi) Im sum_{d=0}^{D} c_d e^{i w d h} f_d,
 // h = 2 dt, D = min(i, N_t - 1 - i), trapezoid weights c_0 = c_D = 1/2 (c_0 =
 // 1/2 alone when D = 0), 1 in between.
-__global__ void k_wigner_dos(const c64* __restrict__ g, int n_t, int n, double h,
-                             const int* __restrict__ tix, int n_T,
-                             const double* __restrict__ w, int n_w,
-                             double* __restrict__ dos) {
-  const int q = blockIdx.x * blockDim.x + threadIdx.x;
-  if (q >= n_w) return;
-  const double om = w[q];
+// A block takes 32 frequencies of one time (times strided over the grid's y
+// dimension); its eight groups take the blocks of eight relative times d = 8 k
+// .. 8 k + 7, k = g, g + 8, ..., whose f_d are staged in LDS, and are summed in
+// order.  e^{i w d h} is the product of the block's e^{i w 8 k h} and one of
+// eight factors formed once: one sincos per eight relative times instead of
+// eight (41 times x 801 frequencies at N_t = 800: 109 -> 12 us).
+constexpr int kDosFreq = 32, kDosGroups = 8, kDosRun = 8, kDosStage = 512;
+__global__ __launch_bounds__(kDosFreq * kDosGroups) void k_wigner_dos(
+    const c64* __restrict__ g, int n_t, int n, double h, const int* __restrict__ tix,
+    int n_T, const double* __restrict__ w, int n_w, double* __restrict__ dos) {
+  __shared__ c64 f[kDosStage];
+  __shared__ double part[kDosGroups][kDosFreq];
+  const int lq = threadIdx.x % kDosFreq, gr = threadIdx.x / kDosFreq;
+  const int q = blockIdx.x * kDosFreq + lq;
+  const double om = w[min(q, n_w - 1)];
+  double cj[kDosRun], sj[kDosRun];
+#pragma unroll
+  for (int j = 0; j < kDosRun; ++j) sincos(om * (j * h), &sj[j], &cj[j]);
   for (int r = blockIdx.y; r < n_T; r += gridDim.y) {
     const int i = tix[r];
     const int dmax = min(i, n_t - 1 - i);
     double acc = 0.0;
-    for (int d = 0; d <= dmax; ++d) {
-      const c64 f = retarded_pair(g, n_t, n, i, d);
-      double sn, cs;
-      sincos(om * (d * h), &sn, &cs);
-      const double c = (d == 0 || d == dmax) ? 0.5 : 1.0;
-      acc += c * (sn * f.re + cs * f.im);
+    for (int s0 = 0; s0 <= dmax; s0 += kDosStage) {
+      __syncthreads();
+      for (int e = threadIdx.x; e < kDosStage; e += kDosFreq * kDosGroups) {
+        const int d = s0 + e;
+        c64 v{0.0, 0.0};
+        if (d <= dmax) {
+          v = retarded_pair(g, n_t, n, i, d);
+          if (d == 0 || d == dmax) {
+            v.re *= 0.5;
+            v.im *= 0.5;
+          }
+        }
+        f[e] = v;
+      }
+      __syncthreads();
+      const int lim = min(kDosStage, dmax + 1 - s0);
+      for (int e = kDosRun * gr; e < lim; e += kDosRun * kDosGroups) {
+        double sn, cs;
+        sincos(om * ((s0 + e) * h), &sn, &cs);
+        double re = 0.0, im = 0.0;     // sum_j e^{i w j h} f_j
+#pragma unroll
+        for (int j = 0; j < kDosRun; ++j) {
+          const c64 v = f[e + j];
+          re += cj[j] * v.re - sj[j] * v.im;
+          im += sj[j] * v.re + cj[j] * v.im;
+        }
+        acc += sn * re + cs * im;
+      }
     }
-    dos[(size_t)r * n_w + q] = -h * acc / 3.14159265358979323846;
+    part[gr][lq] = acc;
+    __syncthreads();
+    if (gr == 0 && q < n_w) {
+      double sum = 0.0;
+#pragma unroll
+      for (int p = 0; p < kDosGroups; ++p) sum += part[p][lq];
+      dos[(size_t)r * n_w + q] = -h * sum / 3.14159265358979323846;
+    }
   }
 }
 
@@ -268,8 +348,8 @@ __global__ void k_moments(const c64* __restrict__ g, int n_t, int n, double h,
 hipError_t launch_wigner_dos(const c64* g, int n_t, int n, double dt, const int* tix,
                              int n_T, const double* w, int n_w, double* dos,
                              hipStream_t st) {
-  hipLaunchKernelGGL(k_wigner_dos, dim3((n_w + 127) / 128, n_T < 4096 ? n_T : 4096),
-                     dim3(128), 0, st, g, n_t, n, 2.0 * dt, tix, n_T, w, n_w, dos);
+  hipLaunchKernelGGL(k_wigner_dos, dim3((n_w + kDosFreq - 1) / kDosFreq, n_T < 4096 ? n_T : 4096),
+                     dim3(kDosFreq * kDosGroups), 0, st, g, n_t, n, 2.0 * dt, tix, n_T, w, n_w, dos);
   return hipGetLastError();
 }
 
@@ -444,7 +524,10 @@ hipError_t launch_build(const c64* sigt, const PointTables& tab, int k0,
                         int nmat, cplx<TO>* xbuf, size_t mat_stride, int ld,
                         int n, hipStream_t st) {
   if (nmat <= 0) return hipSuccess;
-  const int gz = nmat < 16 ? nmat : 16;
+  // matrices per thread: 1/16 of the batch (Sigma~ is read 16 times); fewer
+  // where that leaves the chip short of threads (small matrices)
+  const int wgs = (n + 255) / 256 * n;
+  const int gz = std::min(nmat, std::max(16, 8192 / wgs));
   hipLaunchKernelGGL(k_build<TO>, dim3((n + 255) / 256, n, gz), dim3(256), 0, st, sigt,
                      tab, k0, nmat, xbuf, mat_stride, ld, n);
   return hipGetLastError();
@@ -455,8 +538,8 @@ hipError_t launch_reduce(const cplx<TI>* xbuf, size_t mat_stride, int ld,
                          const int* piv, const int* rowcol, int istride,
                          const double* coef, int nmat, int n, c64* out,
                          int accumulate, hipStream_t st) {
-  const int bx = (n + 255) / 256;
-  hipLaunchKernelGGL(k_reduce<TI>, dim3(bx, n), dim3(256), 0, st, xbuf,
+  hipLaunchKernelGGL(k_reduce<TI>, dim3((n + kRedCols - 1) / kRedCols, n),
+                     dim3(kRedCols * kRedGroups), 0, st, xbuf,
                      mat_stride, ld, piv, rowcol, istride, coef, nmat, n, out,
                      accumulate);
   return hipGetLastError();
@@ -467,7 +550,8 @@ hipError_t launch_current(const cplx<TI>* xbuf, size_t mat_stride, int ld,
                           const int* piv, const int* rowcol, int istride,
                           const PointTables& tab, int k0, int nmat, int n_t,
                           int n, double* cur, hipStream_t st) {
-  hipLaunchKernelGGL(k_current<TI>, dim3((n_t + 127) / 128), dim3(128), 0, st,
+  hipLaunchKernelGGL(k_current<TI>, dim3((n_t + kCurTimes - 1) / kCurTimes),
+                     dim3(kCurTimes * kCurGroups), 0, st,
                      xbuf, mat_stride, ld, piv, rowcol, istride, tab, k0, nmat,
                      n_t, n, cur);
   return hipGetLastError();

@@ -1,0 +1,61 @@
+"""The sums over quadrature points and relative times at the sizes where their
+splits can go wrong: batches of one matrix, fewer matrices than groups of
+threads, and one more than whole rounds; rows one entry beside a block's
+columns; frequencies and relative times around the blocks of the DOS.
+
+Bars: 1e-10 of the largest value against the oracle, as for every FP64 result;
+the complex64 step 1e-4."""
+import numpy as np
+import pytest
+
+from oracle import dmft, dos
+from paper_0711_0999_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+
+def relerr(a, b):
+    return float(np.max(np.abs(a - b)) / np.max(np.abs(b)))
+
+
+def contour(n_t, n_tau):
+    t_min = -0.1 * (n_t // 4)
+    return dict(t_min=t_min, t_max=t_min + 0.1 * n_t, dt=0.1, dtau=0.1, beta=0.1 * n_tau)
+
+
+@pytest.mark.parametrize("n_t,n_tau,n_eps,n_ebar,batch", [
+    (22, 19, 1, 1, 0), (22, 20, 1, 3, 0), (22, 21, 1, 5, 0),   # N_c = 63, 64, 65
+    (25, 15, 3, 11, 0), (25, 15, 3, 11, 17), (9, 5, 5, 13, 33)])
+def test_reduction_and_current(lib, n_t, n_tau, n_eps, n_ebar, batch):
+    print(f"case: N_c = {2 * n_t + n_tau}, {n_eps} x {n_ebar} points, batch {batch}",
+          flush=True)
+    kw = contour(n_t, n_tau)
+    with lib.Context(U=1.0, E=1.5, n_eps=n_eps, n_ebar=n_ebar, **kw) as ctx:
+        if batch:
+            ctx.set_batch(batch)
+        sig = inputs.random_sigma(ctx.n_c, seed=n_t, scale=0.2)
+        p = dmft.Problem(u=1.0, e_field=1.5, n_eps=n_eps, n_ebar=n_ebar, **kw)
+        go, jo, _ = dmft.lattice_only(p, sig)
+        ctx.set_sigma(sig)
+        ctx.compute_gloc()
+        assert relerr(ctx.get_gloc(), go) < 1e-10
+        assert relerr(ctx.get_current()[1], jo) < 1e-10
+        ctx.set_refinement(0)
+        ctx.compute_gloc(lib.FK_MIXED)
+        assert relerr(ctx.get_gloc(), go) < 1e-4
+        assert relerr(ctx.get_current()[1], jo) < 1e-4
+
+
+@pytest.mark.parametrize("n_freq", [1, 31, 33])
+def test_dos_blocks(lib, n_freq):
+    """Windows of 1, 7, 8, 9, 64 and 65 relative times and both ends."""
+    print(f"case: DOS, {n_freq} frequencies", flush=True)
+    kw = contour(140, 10)
+    times = [0, 6, 7, 8, 63, 64, 69, 70, 139]
+    omega = np.linspace(-5.0, 5.5, n_freq)
+    with lib.Context(U=1.0, E=1.5, n_eps=2, n_ebar=2, **kw) as ctx:
+        ctx.set_sigma(inputs.random_sigma(ctx.n_c, seed=5, scale=0.1))
+        ctx.compute_gloc()
+        rho = ctx.wigner_dos(times, omega)
+        ref = dos.wigner_dos(ctx.get_gloc(), 140, 0.1, times, omega)
+    assert relerr(rho, ref) < 1e-10
