@@ -843,24 +843,35 @@ __global__ __launch_bounds__(128 * WR, 4 / WR) void k_update(
     const int* rowcol = rowcolbuf + d.ioff;
     P tp;
     tp.begin(lds, xm + J0, ld, r0, n, bbuf + d.boff + (size_t)ti.b0 * ld, ld, c0, n, wO);
-    // pivot columns of the rows this lane writes
-    int rcv[2][4];
-#pragma unroll
-    for (int ii = 0; ii < 2; ++ii)
-#pragma unroll
-      for (int v = 0; v < 4; ++v) rcv[ii][v] = rowcol[min(tp.row(ii, v), n - 1)];
     tp.run(lds);
-    typename P::c2 cv[2][2][4], *xc = reinterpret_cast<typename P::c2*>(xm);
-    tp.for_each_output([&](int ii, int jj, int v, bool in, unsigned off) {
-      if (in) cv[ii][jj][v] = *at_byte(xc, off);
-    });
-    tp.for_each_output([&](int ii, int jj, int v, bool in, unsigned off) {
-      const bool keep = !(rcv[ii][v] >= J0 && rcv[ii][v] < J0 + wO);
-      typename P::c2 c = tp.value(ii, jj, v);
-      c.x += keep ? cv[ii][jj][v].x : T(0);
-      c.y += keep ? cv[ii][jj][v].y : T(0);
-      if (in) *at_byte(xc, off) = c;
-    });
+    typename P::c2* xc = reinterpret_cast<typename P::c2*>(xm);
+    // C and the pivot columns of the rows this lane writes: all at once in FP64;
+    // by halves in complex64, whose 120 registers (instead of 146) let four
+    // workgroups share a CU (85.5 -> 83.1 ms for 225 matrices of N_c = 1800;
+    // FP64 by halves: 155.9 -> 157.2)
+    constexpr int kRows = sizeof(T) == 8 ? 2 : 1;
+#pragma unroll
+    for (int i0 = 0; i0 < 2; i0 += kRows) {
+      int rcv[kRows][4];
+      typename P::c2 cv[kRows][2][4];
+#pragma unroll
+      for (int q = 0; q < kRows; ++q) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) rcv[q][v] = rowcol[min(tp.row(i0 + q, v), n - 1)];
+        tp.for_outputs(i0 + q, [&](int, int jj, int v, bool in, unsigned off) {
+          if (in) cv[q][jj][v] = *at_byte(xc, off);
+        });
+      }
+#pragma unroll
+      for (int q = 0; q < kRows; ++q)
+        tp.for_outputs(i0 + q, [&](int ii, int jj, int v, bool in, unsigned off) {
+          const bool keep = !(rcv[q][v] >= J0 && rcv[q][v] < J0 + wO);
+          typename P::c2 c = tp.value(ii, jj, v);
+          c.x += keep ? cv[q][jj][v].x : T(0);
+          c.y += keep ? cv[q][jj][v].y : T(0);
+          if (in) *at_byte(xc, off) = c;
+        });
+    }
     if (per < hi - lo) __syncthreads();   // LDS free for the next item
   }
 }

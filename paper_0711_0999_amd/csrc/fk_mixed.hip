@@ -54,12 +54,14 @@ __global__ __launch_bounds__(256, 2) void k_bgemm(
   tp.run(lds);
   P::c2* cm = reinterpret_cast<P::c2*>(C + ss * m);
   const P::c2* im = reinterpret_cast<const P::c2*>(Cin + ss * m);
-  tp.for_each_output([&](int ii, int jj, int v, bool in, unsigned off) {
-    if (!in) return;
-    P::c2 c = tp.value(ii, jj, v);
-    if (beta != 0.0) c += beta * *at_byte(im, off);
-    *at_byte(cm, off) = c;
-  });
+#pragma unroll
+  for (int ii = 0; ii < 2; ++ii)
+    tp.for_outputs(ii, [&](int, int jj, int v, bool in, unsigned off) {
+      if (!in) return;
+      P::c2 c = tp.value(ii, jj, v);
+      if (beta != 0.0) c += beta * *at_byte(im, off);
+      *at_byte(cm, off) = c;
+    });
 }
 
 // R = I - T X + P in place of P (P = Sigma_t X), T = i I + sub-diagonal tsub

@@ -245,8 +245,9 @@ template <typename T, int WR> struct TileProduct {
   __device__ __forceinline__ int row(int ii, int v) const {
     return r0 + (edge ? strip_row() : 32 * wr) + 16 * ii + Mfma<T>::drow(lk, v);
   }
-  // f(ii, jj, v, inside, byte offset in C) for this lane's outputs
-  template <typename F> __device__ __forceinline__ void for_each_output(F f) const {
+  // f(ii, jj, v, inside, byte offset in C) for this lane's outputs of block row
+  // ii (0 or 1; a strip has only 0)
+  template <typename F> __device__ __forceinline__ void for_outputs(int ii, F f) const {
     constexpr unsigned E = sizeof(cplx<T>);
     if (!edge) {
       const int col = c0 + 32 * wc + li;
@@ -254,14 +255,12 @@ template <typename T, int WR> struct TileProduct {
       const unsigned step = (unsigned)(Mfma<T>::drow(0, 1)) * ldc * E;   // v -> v + 1
       const bool whole = r0 + TR <= rows && c0 + kTile <= cols;
 #pragma unroll
-      for (int ii = 0; ii < 2; ++ii)
+      for (int v = 0; v < 4; ++v)
 #pragma unroll
-        for (int v = 0; v < 4; ++v)
-#pragma unroll
-          for (int jj = 0; jj < 2; ++jj)
-            f(ii, jj, v, whole || (row(ii, v) < rows && col + 16 * jj < cols),
-              off + 16u * ii * ldc * E + v * step + 16u * jj * E);
-    } else if (strip_active()) {
+        for (int jj = 0; jj < 2; ++jj)
+          f(ii, jj, v, whole || (row(ii, v) < rows && col + 16 * jj < cols),
+            off + 16u * ii * ldc * E + v * step + 16u * jj * E);
+    } else if (ii == 0 && strip_active()) {
       const int col = c0 + strip_col() + li;
 #pragma unroll
       for (int v = 0; v < 4; ++v)
