@@ -54,6 +54,8 @@ template <typename T> struct Batch {
   size_t stride = 0;
   cplx<T>* x = nullptr;
   cplx<T>* bbuf = nullptr;     // gathered pivot rows, kBRows x ld per matrix
+  cplx<T>* side = nullptr;     // split panels' pivot rows, kNBO x kNBO per matrix
+  size_t side_cap = 0;         // (batches of at most kSplitMats matrices)
   int* piv = nullptr;
   int* rowcol = nullptr;
   int* status = nullptr;
@@ -83,6 +85,7 @@ template <typename T> void batch_free(Batch<T>& b) {
     if (b.piv) (void)hipFree(b.piv);
     if (b.rowcol) (void)hipFree(b.rowcol);
   }
+  if (b.side) (void)hipFree(b.side);
   if (b.status) (void)hipFree(b.status);
   if (b.descs) (void)hipFree(b.descs);
   if (b.items) (void)hipFree(b.items);
@@ -176,6 +179,16 @@ inline double push_tiles(std::vector<TileItem>& it, int m, int n, int tr_rows, i
   return flops;
 }
 
+template <typename P> hipError_t grow(P** ptr, size_t* cap, size_t want) {
+  if (*ptr && *cap >= want) return hipSuccess;
+  if (*ptr) (void)hipFree(*ptr);
+  *ptr = nullptr;
+  *cap = 0;
+  hipError_t e = hipMalloc(ptr, sizeof(P) * std::max<size_t>(want, 1));
+  if (e == hipSuccess) *cap = want;
+  return e;
+}
+
 // Allocate a uniform batch of cap n x n matrices.  On any failure every buffer
 // is released and the batch is left empty (cap 0, x null), so a caller that
 // checks x and cap reallocates instead of launching on a partial batch.
@@ -200,6 +213,9 @@ hipError_t batch_alloc_parts(Batch<T>& b, int cap, int n, int variant) {
   hipError_t e;
   if ((e = hipMalloc(&b.x, sizeof(cplx<T>) * b.stride * cap)) != hipSuccess) return e;
   if ((e = hipMalloc(&b.bbuf, sizeof(cplx<T>) * (size_t)kBRows * b.ld * cap)) != hipSuccess)
+    return e;
+  if (cap <= kSplitMats &&
+      (e = grow(&b.side, &b.side_cap, (size_t)kNBO * kNBO * cap)) != hipSuccess)
     return e;
   if ((e = hipMalloc(&b.piv, sizeof(int) * (size_t)n * cap)) != hipSuccess) return e;
   if ((e = hipMalloc(&b.rowcol, sizeof(int) * (size_t)n * cap)) != hipSuccess) return e;
@@ -243,16 +259,6 @@ hipError_t batch_alloc_parts(Batch<T>& b, int cap, int n, int variant) {
   return hipSuccess;
 }
 
-template <typename P> hipError_t grow(P** ptr, size_t* cap, size_t want) {
-  if (*ptr && *cap >= want) return hipSuccess;
-  if (*ptr) (void)hipFree(*ptr);
-  *ptr = nullptr;
-  *cap = 0;
-  hipError_t e = hipMalloc(ptr, sizeof(P) * std::max<size_t>(want, 1));
-  if (e == hipSuccess) *cap = want;
-  return e;
-}
-
 // Configure the batch for matrices of sizes n[m] (ld = n[m]) packed back to
 // back.  status_idx[m] is the slot of matrix m in the status array passed to
 // batch_invert (the caller zeroes it).  Buffers grow as needed and are kept.
@@ -287,6 +293,9 @@ hipError_t batch_setup_uneven(Batch<T>& b, const std::vector<int>& n,
   hipError_t e;
   if ((e = grow(&b.x, &b.x_cap, xo)) != hipSuccess) return e;
   if ((e = grow(&b.bbuf, &b.b_cap, bo)) != hipSuccess) return e;
+  if (nm <= kSplitMats &&
+      (e = grow(&b.side, &b.side_cap, (size_t)kNBO * kNBO * nm)) != hipSuccess)
+    return e;
   size_t ic = b.i_cap;
   if ((e = grow(&b.piv, &ic, io)) != hipSuccess) return e;
   ic = b.i_cap;
@@ -368,10 +377,10 @@ hipError_t batch_invert(Batch<T>& b, int nmat, hipStream_t st, const Aux& ax,
   if (!status && (e = fill_int(b.status, 0, (size_t)nmat, st)) != hipSuccess) return e;
   if (ev_steps && (e = hipEventRecord(ev_steps[0], st)) != hipSuccess) return e;
   int nl = 0;
-  if ((e = gje_panel<T>(b.x, b.piv, b.rowcol, b.descs, nmat, b.nmax, 0, stat, st)) !=
-      hipSuccess)
+  cplx<T>* side = (size_t)nmat * kNBO * kNBO <= b.side_cap ? b.side : nullptr;
+  if ((e = gje_panel<T>(b.x, b.piv, b.rowcol, b.descs, nmat, b.nmax, 0, stat, side, st,
+                        &nl)) != hipSuccess)
     return e;
-  ++nl;
   auto items_of = [&](int q, int S, int* count) {
     *count = b.uniform ? nmat * b.cnt[q][S] : b.tot[q][S];
     return b.items + b.off[q][S];
@@ -404,10 +413,9 @@ hipError_t batch_invert(Batch<T>& b, int nmat, hipStream_t st, const Aux& ax,
         if ((e = hipEventRecord(ax.evN, st)) != hipSuccess) return e;
         if ((e = hipStreamWaitEvent(ax.st2, ax.evN, 0)) != hipSuccess) return e;
       }
-      if ((e = gje_panel<T>(b.x, b.piv, b.rowcol, b.descs, nmat, b.nmax, S + 1, stat,
-                            ps)) != hipSuccess)
+      if ((e = gje_panel<T>(b.x, b.piv, b.rowcol, b.descs, nmat, b.nmax, S + 1, stat, side,
+                            ps, &nl)) != hipSuccess)
         return e;
-      ++nl;
       if (ax.lookahead && (e = hipEventRecord(ax.evP, ax.st2)) != hipSuccess) return e;
     }
     int nB = 0;

@@ -132,7 +132,7 @@ template <typename T, int KW> struct PivotRows {
 // products and before its stores, so that no load ever waits for a store.
 // FULL: w = KW and cw = 32 (no lane masks, loads that are always issued).
 // Products in the three-product form of the trailing update.
-template <typename T, int KW, bool FULL, typename V>
+template <typename T, int KW, int NW, bool FULL, typename V>
 __device__ __forceinline__ void block_update_as(const V& x, int m,
                              const int* __restrict__ pcol, int j0, int jp, int w,
                              int c0, int cw, int skip,
@@ -191,7 +191,7 @@ __device__ __forceinline__ void block_update_as(const V& x, int m,
   load_m(a, wave, 0);
   if (kNextC) load_c(ct, wave);
 #pragma unroll 1
-  for (int t = wave; t < nt; t += kPW) {
+  for (int t = wave; t < nt; t += NW) {
     if (!kNextC) load_c(ct, t);
     v4 p1[2], p2[2], p3[2];
 #pragma unroll
@@ -210,8 +210,8 @@ __device__ __forceinline__ void block_update_as(const V& x, int m,
       }
       // the next step (past the last one: rows clamped, values unused)
       if (ch + 1 < NCH) load_m(mn, t, ch + 1);
-      else load_m(mn, t + kPW, 0);
-      if (kNextC) load_c(cn, t + kPW);
+      else load_m(mn, t + NW, 0);
+      if (kNextC) load_c(cn, t + NW);
 #pragma unroll
       for (int s = 0; s < KS; ++s) {
         // the next k-step's B is read during this one's products; the fence
@@ -264,15 +264,15 @@ __device__ __forceinline__ void block_update_as(const V& x, int m,
     if (kNextC) ct = cn;
   }
 }
-template <typename T, int KW, typename V>
+template <typename T, int KW, int NW = kPW, typename V>
 __device__ __forceinline__ void block_update(const V& x, int m,
                              const int* __restrict__ pcol, int j0, int jp, int w,
                              int c0, int cw, int skip,
                              const PivotRows<T, kNB>& B) {
   if (w == KW && cw == 32)
-    block_update_as<T, KW, true>(x, m, pcol, j0, jp, w, c0, cw, skip, B);
+    block_update_as<T, KW, NW, true>(x, m, pcol, j0, jp, w, c0, cw, skip, B);
   else
-    block_update_as<T, KW, false>(x, m, pcol, j0, jp, w, c0, cw, skip, B);
+    block_update_as<T, KW, NW, false>(x, m, pcol, j0, jp, w, c0, cw, skip, B);
 }
 
 // B of block_update: row l, column c = value of list entry pive[l] (the pivot
@@ -531,11 +531,16 @@ __device__ __forceinline__ void eliminate_columns(const V& x, const int* rows, i
 // quarter of its 64-column half and the halves to each other by updates with
 // KW = 32 and 64.  QR > 0: at most QR rows; the quarter is kept in LDS while
 // it is factored, so that its groups meet LDS latencies instead of memory's.
-template <typename T, int RPT, int IB, int QR>
+// One matrix of N_c = 1800: 1359 -> 695 us per block on average over the
+// blocks; 100 matrices of N_c = 150: 370 -> 130 us; 225 of N_c = 1800: 1636 ->
+// 1250 us, where the quarters' passes are bound by memory traffic.
+// SPLIT: only quarter `only`, on the same rows; the joins are launches of
+// k_cross, for which the quarter's pivot rows are copied aside.
+template <typename T, int RPT, int IB, int QR, bool SPLIT>
 __global__ __launch_bounds__(kPanelThreads, 1) void k_outer_panel(
     cplx<T>* __restrict__ xbuf, int* __restrict__ pivbuf,
     int* __restrict__ rowcolbuf, const MatDesc* __restrict__ descs, int S,
-    int* __restrict__ status) {
+    int* __restrict__ status, int only, cplx<T>* __restrict__ side) {
   constexpr int kCap = QR > 0 ? QR : RPT * kPanelThreads;
   static_assert(kCap <= RPT * kPanelThreads, "panel rows");
   __shared__ PivotRows<T, kNB> B;
@@ -550,18 +555,19 @@ __global__ __launch_bounds__(kPanelThreads, 1) void k_outer_panel(
   const MatDesc d = descs[blockIdx.x];
   const int n = d.n;
   const int J0 = S * kNBO;
-  if (J0 >= n) return;
+  if (J0 >= n || (SPLIT && J0 + 32 * only >= n)) return;
   int* piv = pivbuf + d.ioff;
   int* rowcol = rowcolbuf + d.ioff;
   int* st = status + d.status_idx;
 
-  // list the unpivoted rows in ascending order (wave ballots, then offsets);
+  // list the rows not pivoted before the block (wave ballots, then offsets);
   // m = n - J0 <= kCap: every earlier column pivoted one row
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   int m = 0;
   for (int r0 = 0, b = 0; r0 < n; r0 += kPanelThreads, b ^= 1) {
     const int r = r0 + tid;
-    const unsigned long long bal = __ballot(r < n && rowcol[min(r, n - 1)] < 0);
+    const int rc = rowcol[min(r, n - 1)];
+    const unsigned long long bal = __ballot(r < n && (rc < 0 || (SPLIT && rc >= J0)));
     if (lane == 0) cnt[b][wave] = (int)__popcll(bal);
     __syncthreads();
     int pos = m + (int)__popcll(bal & ((1ull << lane) - 1ull));
@@ -574,7 +580,7 @@ __global__ __launch_bounds__(kPanelThreads, 1) void k_outer_panel(
     if (((bal >> lane) & 1ull) && pos < kCap) {
       rows[pos] = r;
       roff[pos] = (unsigned)r * (unsigned)d.ld * (unsigned)sizeof(cplx<T>);
-      pcol[pos] = -1;
+      pcol[pos] = rc;
     }
   }
   m = min(m, kCap);
@@ -585,7 +591,7 @@ __global__ __launch_bounds__(kPanelThreads, 1) void k_outer_panel(
 #pragma unroll
   for (int i = 0; i < RPT; ++i) {
     const int e = tid + i * kPanelThreads;
-    place[i] = e < m ? place_mask(kCap) - e : -1;
+    place[i] = e < m && (!SPLIT || pcol[e] < 0) ? place_mask(kCap) - e : -1;
   }
 
   const int J1 = J0 + kNB;
@@ -634,6 +640,22 @@ __global__ __launch_bounds__(kPanelThreads, 1) void k_outer_panel(
     }
     __syncthreads();
   };
+  if constexpr (SPLIT) {
+    const int c0 = J0 + 32 * only, cw = min(32, n - c0);
+    if constexpr (QR > 0) {
+      copy_quarter(c0, cw, false);
+      quarter(InLds<T>{stage}, 0, c0, cw);
+      copy_quarter(c0, cw, true);
+    } else {
+      quarter(x, c0, c0, cw);
+    }
+    cplx<T>* out = side + (size_t)blockIdx.x * kNBO * kNBO + (size_t)(c0 - J0) * kNBO;
+    for (int e = tid; e < cw * kNBO; e += kPanelThreads) {
+      const int l = e / kNBO, c = e % kNBO;
+      if (J0 + c < n) out[e] = *x.at(x.ref(pive[c0 - J0 + l], J0 + c));
+    }
+    return;
+  }
 #pragma unroll 1
   for (int qi = 0; qi < 6; ++qi) {
     // steps 0, 1, 3, 4: the quarters; 2 and 5: left half to right and back
@@ -656,6 +678,51 @@ __global__ __launch_bounds__(kPanelThreads, 1) void k_outer_panel(
     const int dst = (qq & 1) ? c0 - 32 : c0 + 32;
     if (dst < n) cross32(c0, cw, dst, min(32, n - dst));
   }
+}
+
+// Join of a split panel's parts: the columns [co, co + 32 gridDim.z) of block S
+// receive the transform of its KW columns from jo on (offsets in the block) on
+// all rows not pivoted before the block, 64 rows per workgroup; B was copied
+// aside by the quarters' launches.
+template <typename T, int KW>
+__global__ __launch_bounds__(256, 2) void k_cross(
+    cplx<T>* __restrict__ xbuf, const int* __restrict__ rowcolbuf,
+    const cplx<T>* __restrict__ side, const MatDesc* __restrict__ descs, int S, int jo,
+    int co) {
+  __shared__ PivotRows<T, kNB> B;
+  __shared__ unsigned roff[64];
+  __shared__ int pcol[64], count;
+  const MatDesc d = descs[blockIdx.y];
+  const int n = d.n, J0 = S * kNBO, j0 = J0 + jo;
+  const int cz = co + 32 * blockIdx.z, c0 = J0 + cz;
+  const int r0 = 64 * blockIdx.x;
+  if (j0 >= n || c0 >= n || r0 >= n) return;
+  const int w = min(KW, n - j0), cw = min(32, n - c0);
+  const int tid = threadIdx.x;
+  if (tid < 64) {
+    const int r = r0 + tid, rc = rowcolbuf[d.ioff + min(r, n - 1)];
+    const unsigned long long bal = __ballot(r < n && (rc < 0 || rc >= J0));
+    if ((bal >> tid) & 1ull) {
+      const int pos = (int)__popcll(bal & ((1ull << tid) - 1ull));
+      roff[pos] = (unsigned)r * (unsigned)d.ld * (unsigned)sizeof(cplx<T>);
+      pcol[pos] = rc;
+    }
+    if (tid == 0) count = (int)__popcll(bal);
+  }
+  const cplx<T>* src = side + (size_t)blockIdx.y * kNBO * kNBO + (size_t)jo * kNBO + cz;
+  for (int e = tid; e < KW * 32; e += 256) {
+    const int l = e >> 5, c = e & 31;
+    cplx<T> v;
+    v.re = v.im = T(0);
+    if (l < w && c < cw) v = src[l * kNBO + c];
+    B.v[l * kBP + c] = v;
+    B.s[l * kBP + c] = v.re + v.im;
+  }
+  __syncthreads();
+  const int m = count;
+  if (m == 0) return;
+  const InMemory<T> x{xbuf + d.xoff, roff};
+  block_update<T, KW, 4>(x, m, pcol, j0, j0, w, c0, cw, 0, B);
 }
 
 // ------------------------------------------------------------------ gather
@@ -879,24 +946,50 @@ __global__ __launch_bounds__(128 * WR, 4 / WR) void k_update(
 // --------------------------------------------------------------- launchers
 template <typename T>
 hipError_t gje_panel(cplx<T>* x, int* piv, int* rowcol, const MatDesc* d,
-                     int nmat, int nmax, int S, int* status, hipStream_t st) {
+                     int nmat, int nmax, int S, int* status, cplx<T>* side,
+                     hipStream_t st, int* launches) {
   const int left = nmax - S * kNBO;    // rows left of the largest matrix
   if (nmat <= 0 || left <= 0) return hipSuccess;
   if (nmax > kMaxN) return hipErrorInvalidValue;
-  auto go = [&](auto kernel) {
-    hipLaunchKernelGGL(kernel, dim3(nmat), dim3(kPanelThreads), 0, st, x, piv, rowcol, d,
-                       S, status);
-  };
   // by the rows left: quarters of at most 192 (complex64 448) rows stay in
   // LDS; then one, two or four rows per thread; beyond 2048 rows four columns
   // per register block keep the rows in registers
-  if (left <= 192) go(k_outer_panel<T, 1, kIB, 192>);
-  else if (left <= 448 && sizeof(T) == 4) go(k_outer_panel<T, 1, kIB, sizeof(T) == 4 ? 448 : 0>);
-  else if (left <= kPanelThreads) go(k_outer_panel<T, 1, kIB, 0>);
-  else if (left <= 2 * kPanelThreads) go(k_outer_panel<T, 2, kIB, 0>);
-  else if (left <= 4 * kPanelThreads) go(k_outer_panel<T, 4, kIB, 0>);
-  else if (left <= 6 * kPanelThreads) go(k_outer_panel<T, 6, 4, 0>);
-  else go(k_outer_panel<T, kMaxN / kPanelThreads, 4, 0>);
+  auto go = [&](auto split, int only) {
+    constexpr bool SP = decltype(split)::value;
+    auto one = [&](auto kernel) {
+      hipLaunchKernelGGL(kernel, dim3(nmat), dim3(kPanelThreads), 0, st, x, piv, rowcol, d,
+                         S, status, only, side);
+      ++*launches;
+    };
+    if (left <= 192) one(k_outer_panel<T, 1, kIB, 192, SP>);
+    else if (left <= 448 && sizeof(T) == 4) one(k_outer_panel<T, 1, kIB, sizeof(T) == 4 ? 448 : 0, SP>);
+    else if (left <= kPanelThreads) one(k_outer_panel<T, 1, kIB, 0, SP>);
+    else if (left <= 2 * kPanelThreads) one(k_outer_panel<T, 2, kIB, 0, SP>);
+    else if (left <= 4 * kPanelThreads) one(k_outer_panel<T, 4, kIB, 0, SP>);
+    else if (left <= 6 * kPanelThreads) one(k_outer_panel<T, 6, 4, 0, SP>);
+    else one(k_outer_panel<T, kMaxN / kPanelThreads, 4, 0, SP>);
+  };
+  // few matrices leave most CUs idle while one CU each joins the panel's
+  // parts: the joins then run as launches over all row tiles
+  if (!side || nmat > kSplitMats || left <= kSplitRows) {
+    go(std::false_type{}, 0);
+    return hipGetLastError();
+  }
+  auto cross = [&](auto kernel, int jo, int co, int nz) {
+    if (jo >= left || co >= left) return;
+    hipLaunchKernelGGL(kernel, dim3((nmax + 63) / 64, nmat, nz), dim3(256), 0, st, x, rowcol,
+                       side, d, S, jo, co);
+    ++*launches;
+  };
+  for (int h = 0; h < 2; ++h) {
+    const int o = kNB * h;
+    if (o >= left) break;
+    go(std::true_type{}, 2 * h);
+    cross(k_cross<T, 32>, o, o + 32, 1);
+    if (o + 32 < left) go(std::true_type{}, 2 * h + 1);
+    cross(k_cross<T, 32>, o + 32, o, 1);
+    cross(k_cross<T, kNB>, o, kNB - o, 2);
+  }
   return hipGetLastError();
 }
 
@@ -937,7 +1030,8 @@ hipError_t gje_update(cplx<T>* x, const cplx<T>* bbuf, const int* rowcol,
 
 #define FK_INST(T)                                                            \
   template hipError_t gje_panel<T>(cplx<T>*, int*, int*, const MatDesc*, int, \
-                                   int, int, int*, hipStream_t);              \
+                                   int, int, int*, cplx<T>*, hipStream_t,     \
+                                   int*);                                     \
   template hipError_t gje_gather<T>(const cplx<T>*, cplx<T>*, const int*,     \
                                     const MatDesc*, int, int, hipStream_t);   \
   template hipError_t gje_fix<T>(cplx<T>*, const cplx<T>*, const int*,       \

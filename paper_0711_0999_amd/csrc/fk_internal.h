@@ -55,6 +55,13 @@ constexpr int kKC = 16;          // K chunk of the trailing update
 constexpr int kIB = 8;           // panel columns eliminated in registers at once
 constexpr int kPanelThreads = 512;
 constexpr int kGemmThreads = 256;
+// Panels of at most kSplitMats matrices are split into launches while more
+// than kSplitRows rows are left: one matrix of N_c = 1800 14.4 -> 10.7 ms per
+// impurity update, 25 of N_c = 4100 242.6 -> 225.2 ms per step, 64 complex64
+// ones of N_c = 600 no change; 225 of N_c = 751 would lose 5%, and a quarter
+// that stays in LDS is too short for ten launches.
+constexpr int kSplitMats = 64;
+constexpr int kSplitRows = 192;
 constexpr int kMaxN = 5120;      // largest matrix the inversion supports
 
 // Outer blocks are applied to the columns outside them in groups of up to
@@ -88,13 +95,16 @@ __host__ __device__ inline int block_brow(int n, int S) {
 }
 
 // Outer step S of the blocked in-place Gauss-Jordan inversion, pieces:
-//   panel   one workgroup per matrix factors the outer block [S*kNBO, +kNBO)
+//   panel   one workgroup per matrix factors the outer block [S*kNBO, +kNBO);
+//           with `side` (kNBO x kNBO elements per matrix) and few matrices the
+//           joins of its quarters are launches of their own
 //   gather  copies the pivot rows of block S into the side buffer
 //   fix     the block's columns of the rows pivoted before step S
 //   update  C <- mask(C) + M B on the listed tiles (per-item transform)
 template <typename T>
 hipError_t gje_panel(cplx<T>* x, int* piv, int* rowcol, const MatDesc* d,
-                     int nmat, int nmax, int S, int* status, hipStream_t st);
+                     int nmat, int nmax, int S, int* status, cplx<T>* side,
+                     hipStream_t st, int* launches);
 template <typename T>
 hipError_t gje_gather(const cplx<T>* x, cplx<T>* bbuf, const int* piv,
                       const MatDesc* d, int nmat, int S, hipStream_t st);

@@ -85,3 +85,21 @@ def test_equal_pivot_candidates(lib):
     p = dmft.Problem(u=1.0, e_field=0.0, n_eps=3, n_ebar=3, **kw)
     go = dmft.lattice_only(p, np.zeros((259, 259), complex))[0]
     assert relerr(g, go) < 1e-10
+
+
+@pytest.mark.parametrize("n_c", [193, 449, 513, 1025, 2049])
+def test_split_panels_equal_whole_ones(lib, n_c):
+    """65 matrices in one batch factor each block in one launch, batches of 13
+    in several: the same steps, so G_loc differs by the order of its sum only."""
+    print(f"case: N_c = {n_c}, whole and split panels", flush=True)
+    kw = contour(n_c)
+    with lib.Context(U=1.0, E=1.5, n_eps=5, n_ebar=13, **kw) as ctx:
+        ctx.set_sigma(inputs.random_sigma(n_c, seed=n_c, scale=0.1))
+        ctx.set_refinement(0)
+        for precision, bar in ((lib.FK_FP64, 1e-12), (lib.FK_MIXED, 1e-6)):
+            got = []
+            for batch in (65, 13):
+                assert ctx.set_batch(batch) == batch
+                ctx.compute_gloc(precision)
+                got.append(ctx.get_gloc())
+            assert relerr(got[1], got[0]) < bar
