@@ -275,35 +275,25 @@ template <typename T> fk_status ensure_batch(fk_ctx* c) {
   return FK_OK;
 }
 
-fk_status check_status(fk_ctx* c, const int* d_status, int nmat, int k0,
-                       const char* what) {
-  std::vector<int> s(nmat);
-  HIPCHK(c, hipMemcpyAsync(s.data(), d_status, sizeof(int) * nmat,
-                           hipMemcpyDeviceToHost, c->st));
+// Wait for the stream and read its report: the batch's statuses (an error
+// names the first failed matrix) and the norms' keys.  One small kernel writes
+// it to pinned memory; a copy per array and a wait per check left the GPU idle
+// for about 45 us each.
+fk_status finish(fk_ctx* c, const int* d_status, int nmat, int k0, const char* what) {
+  HIPCHK(c, launch_report(d_status, nmat, c->d_key, c->rep, c->st));
   HIPCHK(c, hipStreamSynchronize(c->st));
-  for (int m = 0; m < nmat; ++m) {
-    if (s[m] > 0)
-      return set_err(c, FK_ESINGULAR, "%s: zero pivot at column %d of matrix %d",
-                     what, s[m] - 1, k0 + m);
-    if (s[m] < 0)
-      return set_err(c, FK_ENONFINITE,
-                     "%s: non-finite pivot at column %d of matrix %d", what,
-                     -s[m] - 1, k0 + m);
-  }
+  const int m = c->rep->index, s = c->rep->status;
+  if (s > 0)
+    return set_err(c, FK_ESINGULAR, "%s: zero pivot at column %d of matrix %d", what, s - 1,
+                   k0 + m);
+  if (s < 0)
+    return set_err(c, FK_ENONFINITE, "%s: non-finite pivot at column %d of matrix %d", what,
+                   -s - 1, k0 + m);
   return FK_OK;
 }
-
-double read_key(fk_ctx* c, fk_status* st) {
-  unsigned long long k = 0;
-  hipError_t e = hipMemcpyAsync(&k, c->d_key, sizeof k, hipMemcpyDeviceToHost, c->st);
-  if (e == hipSuccess) e = hipStreamSynchronize(c->st);
-  if (e != hipSuccess) {
-    *st = set_err(c, FK_EDEVICE, "read norm: %s", hipGetErrorString(e));
-    return 0.0;
-  }
-  *st = FK_OK;
+double report_norm(const fk_ctx* c, int i) {
   double v;
-  memcpy(&v, &k, sizeof v);
+  memcpy(&v, &c->rep->key[i], sizeof v);
   return v;
 }
 
@@ -321,7 +311,26 @@ void invalidate_results(fk_ctx* c) {
   c->have_gloc = false;
 }
 
-template <typename T> fk_status lattice_step(fk_ctx* c, double* ir_out) {
+// What a self-consistency loop wants of a lattice step beside its results: G_loc
+// kept for the next iteration and, from the second one on, delta.
+struct LoopNorms {
+  bool first = true;
+  double delta = 0.0;
+};
+// The step's last report: checks the last batch and G_loc.
+fk_status finish_gloc(fk_ctx* c, const int* d_status, int nmat, int k0, const char* what,
+                      LoopNorms* ln) {
+  HIPCHK(c, launch_gloc_norms(c->d_gloc, ln ? c->d_gprev : nullptr, ln && !ln->first,
+                              (size_t)c->ci.n_c * c->ci.n_c, c->d_key, c->st));
+  const fk_status s = finish(c, d_status, nmat, k0, what);
+  if (s != FK_OK) return s;
+  if (!(report_norm(c, 0) <= std::numeric_limits<double>::max()))
+    return set_err(c, FK_ENONFINITE, "G_loc has non-finite entries");
+  if (ln && !ln->first) ln->delta = report_norm(c, 1);
+  return FK_OK;
+}
+
+template <typename T> fk_status lattice_step(fk_ctx* c, double* ir_out, LoopNorms* ln) {
   invalidate_results(c);
   fk_status s = ensure_batch<T>(c);
   if (s != FK_OK) return s;
@@ -329,8 +338,7 @@ template <typename T> fk_status lattice_step(fk_ctx* c, double* ir_out) {
   const int n = c->ci.n_c;
   for (double& t : c->times) t = 0.0;
   int launches = 0;
-  HIPCHK(c, launch_sigma_weight(c->d_sigma, c->d_w, c->d_sigt, n, c->st));
-  HIPCHK(c, fill_f64(c->d_cur, 0.0, (size_t)c->ci.n_t, c->st));
+  HIPCHK(c, launch_sigma_weight(c->d_sigma, c->d_w, c->d_sigt, n, c->d_cur, c->ci.n_t, c->st));
   for (int k0 = 0; k0 < c->npts; k0 += b.cap) {
     const int nmat = std::min(b.cap, c->npts - k0);
     HIPCHK(c, hipEventRecord(c->ev[0], c->st));
@@ -347,7 +355,9 @@ template <typename T> fk_status lattice_step(fk_ctx* c, double* ir_out) {
     HIPCHK(c, launch_current<T>(b.x, b.stride, b.ld, b.piv, b.rowcol, n, c->tab,
                                 k0, nmat, c->ci.n_t, n, c->d_cur, c->st));
     HIPCHK(c, hipEventRecord(c->ev[3], c->st));
-    s = check_status(c, b.status, nmat, k0, "lattice inversion");
+    const bool last = k0 + nmat == c->npts;
+    s = last ? finish_gloc(c, b.status, nmat, k0, "lattice inversion", ln)
+             : finish(c, b.status, nmat, k0, "lattice inversion");
     if (s != FK_OK) return s;
     if (c->clk.on) clock_collect(c->clk);
     c->times[0] += elapsed(c->ev[0], c->ev[1]);
@@ -356,13 +366,6 @@ template <typename T> fk_status lattice_step(fk_ctx* c, double* ir_out) {
     c->times[6] += elapsed(c->ev[6], c->ev[7]);
   }
   c->times[5] = launches;
-  // non-finite check of G_loc
-  HIPCHK(c, fill_u64(c->d_key, 0ULL, 1, c->st));
-  HIPCHK(c, launch_maxabs(c->d_gloc, nullptr, (size_t)n * n, c->d_key, c->st));
-  double mx = read_key(c, &s);
-  if (s != FK_OK) return s;
-  if (!(mx <= std::numeric_limits<double>::max()))
-    return set_err(c, FK_ENONFINITE, "G_loc has non-finite entries");
   if (ir_out) *ir_out = 0.0;
   c->last_nmat = std::min(b.cap, c->npts - (c->npts - 1) / b.cap * b.cap);
   c->last_k0 = c->npts - c->last_nmat;
@@ -373,7 +376,7 @@ template <typename T> fk_status lattice_step(fk_ctx* c, double* ir_out) {
 
 // Mixed lattice step: complex64 build and inversion, then ir_steps FP64
 // refinement steps X <- X + X (I - A X), FP64 reduction.
-fk_status lattice_step_mixed(fk_ctx* c, double* ir_out) {
+fk_status lattice_step_mixed(fk_ctx* c, double* ir_out, LoopNorms* ln) {
   invalidate_results(c);
   const int n = c->ci.n_c, ir = c->ir_steps;
   const size_t nn = (size_t)n * n;
@@ -408,8 +411,7 @@ fk_status lattice_step_mixed(fk_ctx* c, double* ir_out) {
   int launches = 0;
   double resid = 0.0;
   fk_status s;
-  HIPCHK(c, launch_sigma_weight(c->d_sigma, c->d_w, c->d_sigt, n, c->st));
-  HIPCHK(c, fill_f64(c->d_cur, 0.0, (size_t)c->ci.n_t, c->st));
+  HIPCHK(c, launch_sigma_weight(c->d_sigma, c->d_w, c->d_sigt, n, c->d_cur, c->ci.n_t, c->st));
   for (int k0 = 0; k0 < c->npts; k0 += b.cap) {
     const int nmat = std::min(b.cap, c->npts - k0);
     HIPCHK(c, hipEventRecord(c->ev[0], c->st));
@@ -435,19 +437,12 @@ fk_status lattice_step_mixed(fk_ctx* c, double* ir_out) {
       c64* X = c->ir_x;
       c64* Y = c->ir_y;
       for (int it = 0; it < ir; ++it) {
-        HIPCHK(c, fill_u64(c->d_key, 0ULL, 1, c->st));
         HIPCHK(c, launch_bgemm(c->ir_p, nullptr, 0.0, c->d_sigt, 0, X, n, nmat,
                                c->st));
         HIPCHK(c, launch_residual(c->ir_p, X, c->ir_tsub, c->ir_tcor, n, nmat,
-                                  c->d_key, c->st));
+                                  it == ir - 1 ? c->d_key + 2 : nullptr, c->st));
         HIPCHK(c, launch_bgemm(Y, X, 1.0, X, nn, c->ir_p, n, nmat, c->st));
         std::swap(X, Y);
-        const double r = read_key(c, &s);
-        if (s != FK_OK) return s;
-        // the last step's residual R = I - A X is that of the iterate entering
-        // it; the returned X + X R has the residual R^2 exactly (Newton), whose
-        // entries are at most N_c max|R|^2: that bound is reported
-        if (it == ir - 1) resid = std::max(resid, (double)n * r * r);
       }
       HIPCHK(c, hipEventRecord(c->ev[3], c->st));
       HIPCHK(c, launch_reduce<double>(X, nn, n, c->d_iota, c->d_iota, 0,
@@ -457,8 +452,15 @@ fk_status lattice_step_mixed(fk_ctx* c, double* ir_out) {
                                        k0, nmat, c->ci.n_t, n, c->d_cur, c->st));
     }
     HIPCHK(c, hipEventRecord(c->ev[4], c->st));
-    s = check_status(c, b.status, nmat, k0, "complex64 inversion");
+    const bool last = k0 + nmat == c->npts;
+    s = last ? finish_gloc(c, b.status, nmat, k0, "complex64 inversion", ln)
+             : finish(c, b.status, nmat, k0, "complex64 inversion");
     if (s != FK_OK) return s;
+    // the last step's residual R = I - A X is that of the iterate entering it;
+    // the returned X + X R has the residual R^2 exactly (Newton), whose entries
+    // are at most N_c max|R|^2: that bound is reported
+    const double r = report_norm(c, 2);
+    resid = std::max(resid, (double)n * r * r);
     if (c->clk.on) clock_collect(c->clk);
     c->times[0] += elapsed(c->ev[0], c->ev[1]);
     c->times[1] += elapsed(c->ev[1], c->ev[2]);
@@ -467,12 +469,6 @@ fk_status lattice_step_mixed(fk_ctx* c, double* ir_out) {
     c->times[6] += elapsed(c->ev[6], c->ev[7]);
   }
   c->times[5] = launches;
-  HIPCHK(c, fill_u64(c->d_key, 0ULL, 1, c->st));
-  HIPCHK(c, launch_maxabs(c->d_gloc, nullptr, nn, c->d_key, c->st));
-  const double mx = read_key(c, &s);
-  if (s != FK_OK) return s;
-  if (!(mx <= std::numeric_limits<double>::max()))
-    return set_err(c, FK_ENONFINITE, "G_loc has non-finite entries");
   if (ir_out) *ir_out = resid;
   c->have_gloc = true;
   return FK_OK;
@@ -484,7 +480,6 @@ fk_status impurity(fk_ctx* c, double* dsig) {
   Batch<double>& b = c->imp;
   if (!b.x) HIPCHK(c, batch_alloc(b, 1, n));
   int launches = 0;
-  fk_status s;
   HIPCHK(c, hipEventRecord(c->ev[4], c->st));
   // G0^-1 = (G_loc W)^-1 + Sigma W.  G_imp = (1 - w1) A0^-1 + w1 A1^-1 with
   // A_m = G0^-1 + d_m S has the inverse A1 C^-1 A0, C = (1 - w1) A1 + w1 A0 =
@@ -505,22 +500,18 @@ fk_status impurity(fk_ctx* c, double* dsig) {
   const double dc = (1.0 - w1) * d1 + w1 * d0, h = (1.0 - w1) * d0 + w1 * d1;
   const double gam = w1 * (1.0 - w1) * (d0 - d1) * (d0 - d1);
   c64* X = c->d_g0inv;   // impurity scratch
-  HIPCHK(c, launch_right_weight(c->d_gloc, c->d_w, X, n, n, c->st));
-  HIPCHK(c, launch_right_weight(c->d_sigma, c->d_w, c->d_tmp, n, n, c->st));
+  HIPCHK(c, launch_right_weight(c->d_gloc, X, c->d_sigma, c->d_tmp, c->d_w, n, c->st));
   HIPCHK(c, launch_bgemm(b.x, nullptr, 0.0, c->d_tmp, 0, X, n, 1, c->st));
   HIPCHK(c, launch_add_identity_shift(b.x, b.ld, X, dc, n, c->st));
   HIPCHK(c, batch_invert<double>(b, 1, c->st, c->aux, &launches));
-  if ((s = check_status(c, b.status, 1, 0, "inverse of I + (Sigma W + d S) G_loc W")) !=
-      FK_OK)
-    return s;
   HIPCHK(c, launch_reduce<double>(b.x, b.stride, b.ld, b.piv, b.rowcol, n,
                                   c->d_coef, 1, n, c->d_tmp, 0, c->st));
   HIPCHK(c, launch_bgemm(b.x, nullptr, 0.0, X, 0, c->d_tmp, n, 1, c->st));
-  HIPCHK(c, fill_u64(c->d_key, 0ULL, 1, c->st));
-  HIPCHK(c, launch_sigma_fk(b.x, c->d_w, c->d_sigma, n, h, gam, c->d_key, c->st));
+  HIPCHK(c, launch_sigma_fk(b.x, c->d_w, c->d_sigma, n, h, gam, b.status, c->d_key, c->st));
   HIPCHK(c, hipEventRecord(c->ev[5], c->st));
-  double mx = read_key(c, &s);
+  const fk_status s = finish(c, b.status, 1, 0, "inverse of I + (Sigma W + d S) G_loc W");
   if (s != FK_OK) return s;
+  const double mx = report_norm(c, 0);
   c->times[4] = elapsed(c->ev[4], c->ev[5]);
   if (!(mx <= std::numeric_limits<double>::max()))
     return set_err(c, FK_ENONFINITE, "Sigma has non-finite entries");
@@ -563,6 +554,8 @@ void free_ctx(fk_ctx* c) {
     if (p) (void)hipFree(p);
   if (c->d_iota) (void)hipFree(c->d_iota);
   if (c->d_key) (void)hipFree(c->d_key);
+  if (c->rep) (void)hipHostFree(c->rep);
+  if (c->d_call) (void)hipFree(c->d_call);
   batch_free(c->b64);
   batch_free(c->b32);
   batch_free(c->imp);
@@ -700,7 +693,9 @@ extern "C" fk_status fk_create(const fk_contour* cont, const fk_model* mod,
   if (e == hipSuccess) e = upload(&c->d_sin, sn.data(), sizeof(double) * n_t);
   if (e == hipSuccess) e = upload(&c->d_tpos, tp.data(), sizeof(int) * n_t);
   if (e == hipSuccess) e = upload(&c->d_coef, coef, sizeof coef);
-  if (e == hipSuccess) e = hipMalloc(&c->d_key, sizeof(unsigned long long));
+  if (e == hipSuccess) e = hipMalloc(&c->d_key, sizeof(unsigned long long) * kReportKeys);
+  if (e == hipSuccess) e = hipMemset(c->d_key, 0, sizeof(unsigned long long) * kReportKeys);
+  if (e == hipSuccess) e = hipHostMalloc(&c->rep, sizeof(Report), hipHostMallocDefault);
   if (e == hipSuccess) {
     std::vector<int> iota(n);
     for (int j = 0; j < n; ++j) iota[j] = j;
@@ -825,8 +820,8 @@ extern "C" fk_status fk_set_switch(fk_ctx* c, double switch_tol) {
 
 extern "C" fk_status fk_compute_gloc(fk_ctx* c, fk_precision prec, double* ir_out) {
   if (!c) return FK_EINVAL;
-  if (prec == FK_FP64) return lattice_step<double>(c, ir_out);
-  if (prec == FK_MIXED) return lattice_step_mixed(c, ir_out);
+  if (prec == FK_FP64) return lattice_step<double>(c, ir_out, nullptr);
+  if (prec == FK_MIXED) return lattice_step_mixed(c, ir_out, nullptr);
   return set_err(c, FK_EINVAL, "unknown precision %d", (int)prec);
 }
 
@@ -873,12 +868,24 @@ extern "C" fk_status fk_get_zeroth_moment(const fk_ctx* cc, double* m0) {
 }
 
 namespace {
-// Device copies of small host arrays for the spectral functions: one
-// allocation per call (post-processing, outside the iteration), freed on return.
+// Staging of the spectral functions' small arrays, kept by the context (an
+// allocation and its release took half of a call); beyond kCallKeep bytes it
+// is the call's own.
+constexpr size_t kCallKeep = (size_t)16 << 20;
 struct CallBuffer {
-  void* p = nullptr;
+  char* p = nullptr;
+  bool own = false;
+  hipError_t get(fk_ctx* c, size_t bytes) {
+    if (bytes > kCallKeep) {
+      own = true;
+      return hipMalloc(&p, bytes);
+    }
+    const hipError_t e = grow(&c->d_call, &c->call_cap, bytes);
+    p = c->d_call;
+    return e;
+  }
   ~CallBuffer() {
-    if (p) (void)hipFree(p);
+    if (own && p) (void)hipFree(p);
   }
 };
 }  // namespace
@@ -898,8 +905,8 @@ extern "C" fk_status fk_wigner_dos(const fk_ctx* cc, int n_T, const int* t_index
   const size_t bo = sizeof(double) * (size_t)n_T * n_w;
   const size_t off_w = (bi + 255) / 256 * 256, off_o = off_w + (bw + 255) / 256 * 256;
   CallBuffer buf;
-  HIPCHK(c, hipMalloc(&buf.p, off_o + bo));
-  char* base = static_cast<char*>(buf.p);
+  HIPCHK(c, buf.get(c, off_o + bo));
+  char* base = buf.p;
   HIPCHK(c, hipMemcpyAsync(base, t_index, bi, hipMemcpyHostToDevice, c->st));
   HIPCHK(c, hipMemcpyAsync(base + off_w, omega, bw, hipMemcpyHostToDevice, c->st));
   HIPCHK(c, launch_wigner_dos(c->d_gloc, n_t, n, c->c.dt, reinterpret_cast<int*>(base),
@@ -958,8 +965,8 @@ extern "C" fk_status fk_equal_time_moments(const fk_ctx* cc, int n_T, const int*
   const size_t bi = sizeof(int) * (size_t)n_T, off_o = (bi + 255) / 256 * 256;
   const size_t bo = sizeof(c64) * 3 * (size_t)n_T;
   CallBuffer buf;
-  HIPCHK(c, hipMalloc(&buf.p, off_o + bo));
-  char* base = static_cast<char*>(buf.p);
+  HIPCHK(c, buf.get(c, off_o + bo));
+  char* base = buf.p;
   HIPCHK(c, hipMemcpyAsync(base, t_index, bi, hipMemcpyHostToDevice, c->st));
   HIPCHK(c, launch_moments(c->d_gloc, n_t, n, c->c.dt, reinterpret_cast<int*>(base), n_T,
                            reinterpret_cast<c64*>(base + off_o), c->st));
@@ -982,19 +989,12 @@ namespace {
 fk_status iteration(fk_ctx* c, int it, bool* low, double* delta, double* prev_delta,
                     double* hist, double* dsig) {
   if (*low) c->low_iters++;
-  fk_status s = fk_compute_gloc(c, *low ? FK_MIXED : FK_FP64, nullptr);
+  LoopNorms ln;
+  ln.first = it == 1;
+  fk_status s = *low ? lattice_step_mixed(c, nullptr, &ln) : lattice_step<double>(c, nullptr, &ln);
   if (s != FK_OK) return s;
-  if (it > 1) {
-    HIPCHK(c, fill_u64(c->d_key, 0ULL, 1, c->st));
-    HIPCHK(c, launch_maxabs(c->d_gloc, c->d_gprev, (size_t)c->ci.n_c * c->ci.n_c,
-                            c->d_key, c->st));
-    *delta = read_key(c, &s);
-    if (s != FK_OK) return s;
-  }
+  if (it > 1) *delta = ln.delta;
   if (hist) hist[it - 1] = *delta;
-  HIPCHK(c, hipMemcpyAsync(c->d_gprev, c->d_gloc,
-                           sizeof(c64) * (size_t)c->ci.n_c * c->ci.n_c,
-                           hipMemcpyDeviceToDevice, c->st));
   s = impurity(c, dsig);
   if (s != FK_OK) return s;
   // leave the complex64 phase below switch_tol, or when delta stops
@@ -1042,10 +1042,9 @@ extern "C" fk_status fk_iterate_judged(fk_ctx* c, const double* fallback_dev,
   const c64* fb = reinterpret_cast<const c64*>(fallback_dev);
   fk_status s;
   // size of the proposed move away from the fallback start
-  HIPCHK(c, fill_u64(c->d_key, 0ULL, 1, c->st));
   HIPCHK(c, launch_maxabs(c->d_sigma, fb, nn, c->d_key, c->st));
-  const double move = read_key(c, &s);
-  if (s != FK_OK) return s;
+  if ((s = finish(c, nullptr, 0, 0, "start")) != FK_OK) return s;
+  const double move = report_norm(c, 0);
   double delta = std::numeric_limits<double>::infinity();
   double prev_delta = delta;
   bool low = (prec == FK_MIXED);
@@ -1224,7 +1223,7 @@ extern "C" fk_status fk_autotune(fk_ctx* c, double max_bytes, int keep,
     if (k * ncu < c->npts) add_cap(k * ncu);
   const int n = c->ci.n_c;
   c->last_prec = -1;   // the trials overwrite and free the batch buffers
-  HIPCHK(c, launch_sigma_weight(c->d_sigma, c->d_w, c->d_sigt, n, c->st));
+  HIPCHK(c, launch_sigma_weight(c->d_sigma, c->d_w, c->d_sigt, n, nullptr, 0, c->st));
   int trials = 0;
   fk_status s;
   // one schedule: build and invert one batch twice, the second timed; the
@@ -1248,7 +1247,7 @@ extern "C" fk_status fk_autotune(fk_ctx* c, double max_bytes, int keep,
       HIPCHK(c, hipStreamSynchronize(c->st));
       ms = elapsed(c->ev[0], c->ev[1]);
     }
-    if ((st = check_status(c, b.status, nmat, 0, "autotune inversion")) != FK_OK) return st;
+    if ((st = finish(c, b.status, nmat, 0, "autotune inversion")) != FK_OK) return st;
     *est = (double)ms * ((c->npts + nmat - 1) / nmat);
     ++trials;
     return FK_OK;

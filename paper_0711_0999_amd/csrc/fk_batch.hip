@@ -325,12 +325,12 @@ hipError_t record_sweep(fk_batch* b) {
   for (int id : b->active) {
     fk_ctx* c = b->inst[id];
     const int n = c->ci.n_c;
-    if ((e = launch_sigma_weight(c->d_sigma, c->d_w, c->d_sigt, n, b->st)) != hipSuccess)
+    if ((e = launch_sigma_weight(c->d_sigma, c->d_w, c->d_sigt, n, c->d_cur, c->ci.n_t,
+                                 b->st)) != hipSuccess)
       return e;
     if ((e = fill_f64(reinterpret_cast<double*>(c->d_gloc), 0.0, 2 * (size_t)n * n, b->st)) !=
         hipSuccess)
       return e;
-    if ((e = fill_f64(c->d_cur, 0.0, (size_t)c->ci.n_t, b->st)) != hipSuccess) return e;
   }
   for (Chunk& ch : b->chunks) {
     for (const Segment& sg : ch.segs) {
@@ -376,9 +376,8 @@ hipError_t record_sweep(fk_batch* b) {
     double dc, h, gam;
     imp_shifts(c, &dc, &h, &gam);
     c64* slot = b->xi + b->imp_s0[a];
-    if ((e = launch_right_weight(c->d_gloc, c->d_w, c->d_g0inv, n, n, b->st)) != hipSuccess)
-      return e;
-    if ((e = launch_right_weight(c->d_sigma, c->d_w, c->d_tmp, n, n, b->st)) != hipSuccess)
+    if ((e = launch_right_weight(c->d_gloc, c->d_g0inv, c->d_sigma, c->d_tmp, c->d_w, n,
+                                 b->st)) != hipSuccess)
       return e;
     if ((e = launch_bgemm(slot, nullptr, 0.0, c->d_tmp, 0, c->d_g0inv, n, 1, b->st)) !=
         hipSuccess)
@@ -404,8 +403,8 @@ hipError_t record_sweep(fk_batch* b) {
     if ((e = launch_bgemm(slot, nullptr, 0.0, c->d_g0inv, 0, c->d_tmp, n, 1, b->st)) !=
         hipSuccess)
       return e;
-    if ((e = launch_sigma_fk(slot, c->d_w, c->d_sigma, n, h, gam, b->d_keys + 2 * id + 1,
-                             b->st)) != hipSuccess)
+    if ((e = launch_sigma_fk(slot, c->d_w, c->d_sigma, n, h, gam, nullptr,
+                             b->d_keys + 2 * id + 1, b->st)) != hipSuccess)
       return e;
   }
   return hipSuccess;

@@ -46,7 +46,10 @@ struct fk_ctx {
   double* d_sin = nullptr;
   int* d_tpos = nullptr;
   double* d_coef = nullptr;    // {1, 1 - w1, w1}
-  unsigned long long* d_key = nullptr;
+  unsigned long long* d_key = nullptr;   // kReportKeys norms' keys, zero between uses
+  fk::Report* rep = nullptr;             // pinned host memory
+  char* d_call = nullptr;                // staging of the spectral functions
+  size_t call_cap = 0;
   fk::PointTables tab;
 
   fk::Batch<double> b64;           // lattice batch (complex128)

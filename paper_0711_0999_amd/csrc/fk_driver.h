@@ -28,6 +28,15 @@ __global__ void k_fill_f64(double* p, double v, size_t n) {
     p[e] = v;
 }
 
+// a <- va (na entries), b <- vb (nb entries)
+__global__ void k_fill_two(int* a, int va, size_t na, int* b, int vb, size_t nb) {
+  for (size_t e = blockIdx.x * (size_t)blockDim.x + threadIdx.x; e < na + nb;
+       e += (size_t)gridDim.x * blockDim.x) {
+    if (e < na) a[e] = va;
+    else b[e - na] = vb;
+  }
+}
+
 hipError_t fill_int(int* p, int v, size_t n, hipStream_t st) {
   size_t g = (n + 255) / 256;
   if (g > 4096) g = 4096;
@@ -373,8 +382,10 @@ hipError_t batch_invert(Batch<T>& b, int nmat, hipStream_t st, const Aux& ax,
   hipError_t e;
   int* stat = status ? status : b.status;
   const size_t nints = b.uniform ? (size_t)b.n * nmat : b.nints;
-  if ((e = fill_int(b.rowcol, -1, nints, st)) != hipSuccess) return e;
-  if (!status && (e = fill_int(b.status, 0, (size_t)nmat, st)) != hipSuccess) return e;
+  const size_t nst = status ? 0 : (size_t)nmat;
+  hipLaunchKernelGGL(k_fill_two, dim3((int)std::min<size_t>((nints + nst + 255) / 256, 4096)),
+                     dim3(256), 0, st, b.rowcol, -1, nints, b.status, 0, nst);
+  if ((e = hipGetLastError()) != hipSuccess) return e;
   if (ev_steps && (e = hipEventRecord(ev_steps[0], st)) != hipSuccess) return e;
   int nl = 0;
   cplx<T>* side = (size_t)nmat * kNBO * kNBO <= b.side_cap ? b.side : nullptr;

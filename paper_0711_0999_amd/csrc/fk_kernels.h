@@ -24,8 +24,20 @@ struct PointTables {
   const int* t_pos;
 };
 
+// What a step reports to the host (pinned memory): the first matrix of the last
+// batch with a non-zero status (index = batch size if none), and norms' keys.
+constexpr int kReportKeys = 3;   // max |G_loc| or |dSigma|, delta, refinement residual
+struct Report {
+  int status, index;
+  unsigned long long key[kReportKeys];
+};
+
 hipError_t launch_sigma_weight(const c64* sigma, const c64* w, c64* sigt, int n,
-                               hipStream_t st);
+                               double* cur, int n_t, hipStream_t st);
+hipError_t launch_gloc_norms(const c64* g, c64* prev, int delta, size_t total,
+                             unsigned long long* keys, hipStream_t st);
+hipError_t launch_report(const int* status, int nmat, unsigned long long* keys, Report* rep,
+                         hipStream_t st);
 template <typename TO>
 hipError_t launch_build(const c64* sigt, const PointTables& tab, int k0,
                         int nmat, cplx<TO>* xbuf, size_t mat_stride, int ld,
@@ -52,18 +64,15 @@ hipError_t launch_moments(const c64* g, int n_t, int n, double dt, const int* ti
                           int n_T, c64* mu, hipStream_t st);
 hipError_t launch_equal_time(const c64* g, int n_t, int n, c64* less, c64* greater,
                              hipStream_t st);
-hipError_t launch_right_weight(const c64* src, const c64* w, c64* dst, int ld,
-                               int n, hipStream_t st);
-hipError_t launch_add_right_weighted(c64* g0inv, const c64* sigma, const c64* w,
-                                     int n, hipStream_t st);
-hipError_t launch_shifted_pair(const c64* g0inv, double d0, double d1, c64* x0,
-                               c64* x1, int ld, int n, hipStream_t st);
+hipError_t launch_right_weight(const c64* src0, c64* dst0, const c64* src1, c64* dst1,
+                               const c64* w, int n, hipStream_t st);
 // slot += I + d S X (X natural, n x n; slot with leading dimension ld)
 hipError_t launch_add_identity_shift(c64* slot, int ld, const c64* x, double d, int n,
                                      hipStream_t st);
 // sigma_new = (-h S + gam S X S) W^-1 from X = (G0^-1 + d_c S)^-1 (natural layout)
 hipError_t launch_sigma_fk(const c64* x, const c64* w, c64* sigma, int n, double h,
-                           double gam, unsigned long long* key, hipStream_t st);
+                           double gam, const int* status, unsigned long long* key,
+                           hipStream_t st);
 
 hipError_t launch_ttab(const PointTables& tab, int k0, int nmat, int n,
                        c64* tsub, c64* tcor, hipStream_t st);

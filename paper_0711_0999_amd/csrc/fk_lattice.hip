@@ -16,11 +16,14 @@
 namespace fk {
 
 // ------------------------------------------------------------ Sigma_t ------
-// sigt[i][j] = W_i sigma[i][j] W_j  (both contour integrals of eq. dyson)
+// sigt[i][j] = W_i sigma[i][j] W_j  (both contour integrals of eq. dyson); also
+// clears the n_t <= n entries of the current (nullable)
 __global__ void k_sigma_weight(const c64* __restrict__ sigma,
                                const c64* __restrict__ w, c64* __restrict__ sigt,
-                               int n) {
+                               int n, double* __restrict__ cur, int n_t) {
   const size_t total = (size_t)n * n;
+  if (cur && blockIdx.x == 0)
+    for (int i = threadIdx.x; i < n_t; i += blockDim.x) cur[i] = 0.0;
   for (size_t e = blockIdx.x * (size_t)blockDim.x + threadIdx.x; e < total;
        e += (size_t)gridDim.x * blockDim.x) {
     const int i = (int)(e / n), j = (int)(e - (e / n) * n);
@@ -387,56 +390,80 @@ __global__ void k_maxabs(const c64* __restrict__ a, const c64* __restrict__ b,
   if ((threadIdx.x & 63) == 0) atomicMax(key, k);
 }
 
+// The end of a lattice step in one pass over G_loc: keys[0] takes max |g|
+// (non-finite entries), and in a loop keys[1] takes max |g - prev| (delta) and
+// prev <- g for the next iteration.
+__global__ void k_gloc_norms(const c64* __restrict__ g, c64* __restrict__ prev, int delta,
+                             size_t total, unsigned long long* __restrict__ keys) {
+  constexpr unsigned long long kBad = 0x7ff8000000000000ULL;
+  double m0 = 0.0, m1 = 0.0;
+  bool bad0 = false, bad1 = false;
+  for (size_t e = blockIdx.x * (size_t)blockDim.x + threadIdx.x; e < total;
+       e += (size_t)gridDim.x * blockDim.x) {
+    const c64 v = g[e];
+    const double a = sqrt(v.re * v.re + v.im * v.im);
+    if (!(a <= 1.79769313486231570815e308)) bad0 = true;
+    else if (a > m0) m0 = a;
+    if (delta) {
+      const double dr = v.re - prev[e].re, di = v.im - prev[e].im;
+      const double b = sqrt(dr * dr + di * di);
+      if (!(b <= 1.79769313486231570815e308)) bad1 = true;
+      else if (b > m1) m1 = b;
+    }
+    if (prev) prev[e] = v;
+  }
+  unsigned long long k0 = bad0 ? kBad : (unsigned long long)__double_as_longlong(m0);
+  unsigned long long k1 = bad1 ? kBad : (unsigned long long)__double_as_longlong(m1);
+  for (int off = 32; off >= 1; off >>= 1) {
+    const unsigned long long o0 = __shfl_xor(k0, off), o1 = __shfl_xor(k1, off);
+    k0 = o0 > k0 ? o0 : k0;
+    k1 = o1 > k1 ? o1 : k1;
+  }
+  if ((threadIdx.x & 63) == 0) {
+    atomicMax(keys, k0);
+    if (delta) atomicMax(keys + 1, k1);
+  }
+}
+
+// What the host has to know of a step, in one small write to its memory: the
+// first non-zero status of the batch, and the norms' keys, which are cleared.
+__global__ void k_report(const int* __restrict__ status, int nmat,
+                         unsigned long long* __restrict__ keys, Report* __restrict__ rep) {
+  __shared__ int first;
+  if (threadIdx.x == 0) first = nmat;
+  __syncthreads();
+  for (int m = threadIdx.x; m < nmat; m += blockDim.x)
+    if (status[m] != 0) {
+      atomicMin(&first, m);
+      break;
+    }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    rep->index = first;
+    rep->status = first < nmat ? status[first] : 0;
+  }
+  if (threadIdx.x < kReportKeys) {
+    rep->key[threadIdx.x] = keys[threadIdx.x];
+    keys[threadIdx.x] = 0ULL;
+  }
+}
+
 // ----------------------------------------------------------- impurity ------
-// dst[i][j] = src[i][j] * W_j  (right weighting), stored into an inversion slot
-__global__ void k_right_weight(const c64* __restrict__ src,
-                               const c64* __restrict__ w, c64* __restrict__ dst,
-                               int ld, int n) {
+// dst[i][j] = src[i][j] * W_j (right weighting) of G_loc and Sigma (blockIdx.y)
+__global__ void k_right_weight(const c64* __restrict__ src0, c64* __restrict__ dst0,
+                               const c64* __restrict__ src1, c64* __restrict__ dst1,
+                               const c64* __restrict__ w, int n) {
+  const c64* src = blockIdx.y ? src1 : src0;
+  c64* dst = blockIdx.y ? dst1 : dst0;
   const size_t total = (size_t)n * n;
   for (size_t e = blockIdx.x * (size_t)blockDim.x + threadIdx.x; e < total;
        e += (size_t)gridDim.x * blockDim.x) {
-    const int i = (int)(e / n), j = (int)(e - (e / n) * n);
+    const int j = (int)(e % n);
     const c64 s = src[e], wj = w[j];
     c64 r;
     r.re = s.re * wj.re - s.im * wj.im;
     r.im = s.re * wj.im + s.im * wj.re;
-    dst[(size_t)i * ld + j] = r;
-  }
-}
-
-// g0inv += sigma * W (right-weighted Sigma added to the inverse already there)
-__global__ void k_add_right_weighted(c64* __restrict__ g0inv,
-                                     const c64* __restrict__ sigma,
-                                     const c64* __restrict__ w, int n) {
-  const size_t total = (size_t)n * n;
-  for (size_t e = blockIdx.x * (size_t)blockDim.x + threadIdx.x; e < total;
-       e += (size_t)gridDim.x * blockDim.x) {
-    const int j = (int)(e - (e / n) * n);
-    const c64 s = sigma[e], wj = w[j];
-    c64 g = g0inv[e];
-    g.re += s.re * wj.re - s.im * wj.im;
-    g.im += s.re * wj.im + s.im * wj.re;
-    g0inv[e] = g;
-  }
-}
-
-// slot_m = g0inv + d_m S for m = 0, 1 (S[j][j-1] = 1, S[0][n-1] = -1);
-// x1 may be null (one slot)
-__global__ void k_shifted_pair(const c64* __restrict__ g0inv, double d0,
-                               double d1, c64* __restrict__ x0,
-                               c64* __restrict__ x1, int ld, int n) {
-  const size_t total = (size_t)n * n;
-  for (size_t e = blockIdx.x * (size_t)blockDim.x + threadIdx.x; e < total;
-       e += (size_t)gridDim.x * blockDim.x) {
-    const int i = (int)(e / n), j = (int)(e - (e / n) * n);
-    double s = 0.0;
-    if (j == i - 1) s = 1.0;
-    if (i == 0 && j == n - 1) s = (n == 1) ? 0.0 : -1.0;
-    c64 a = g0inv[e], b = g0inv[e];
-    a.re += d0 * s;
-    b.re += d1 * s;
-    x0[(size_t)i * ld + j] = a;
-    if (x1) x1[(size_t)i * ld + j] = b;
+    dst[e] = r;
   }
 }
 
@@ -468,9 +495,12 @@ hipError_t launch_add_identity_shift(c64* slot, int ld, const c64* x, double d, 
 // G0^-1 - G_imp^-1), sigma_new[i][j] = that / W_j, and the running max of
 // |sigma_new - sigma_old| via the key of k_maxabs.  (S X S)[i][j] =
 // s_i t_j X[i - 1 mod n][j + 1 mod n] with s_0 = t_{n-1} = -1, else 1.
+// Leaves sigma as it is where the inversion failed (status, nullable).
 __global__ void k_sigma_fk(const c64* __restrict__ x, const c64* __restrict__ w,
                            c64* __restrict__ sigma, int n, double h, double gam,
+                           const int* __restrict__ status,
                            unsigned long long* __restrict__ key) {
+  if (status && *status != 0) return;
   const size_t total = (size_t)n * n;
   double mx = 0.0;
   bool bad = false;
@@ -513,9 +543,9 @@ static inline int grid_for(size_t total, int block) {
 }
 
 hipError_t launch_sigma_weight(const c64* sigma, const c64* w, c64* sigt, int n,
-                               hipStream_t st) {
+                               double* cur, int n_t, hipStream_t st) {
   hipLaunchKernelGGL(k_sigma_weight, dim3(grid_for((size_t)n * n, 256)),
-                     dim3(256), 0, st, sigma, w, sigt, n);
+                     dim3(256), 0, st, sigma, w, sigt, n, cur, n_t);
   return hipGetLastError();
 }
 
@@ -564,32 +594,33 @@ hipError_t launch_maxabs(const c64* a, const c64* b, size_t total,
   return hipGetLastError();
 }
 
-hipError_t launch_right_weight(const c64* src, const c64* w, c64* dst, int ld,
-                               int n, hipStream_t st) {
-  hipLaunchKernelGGL(k_right_weight, dim3(grid_for((size_t)n * n, 256)),
-                     dim3(256), 0, st, src, w, dst, ld, n);
+hipError_t launch_gloc_norms(const c64* g, c64* prev, int delta, size_t total,
+                             unsigned long long* keys, hipStream_t st) {
+  const int gr = grid_for(total, 256);
+  hipLaunchKernelGGL(k_gloc_norms, dim3(gr > 2048 ? 2048 : gr), dim3(256), 0, st, g, prev,
+                     delta, total, keys);
   return hipGetLastError();
 }
 
-hipError_t launch_add_right_weighted(c64* g0inv, const c64* sigma, const c64* w,
-                                     int n, hipStream_t st) {
-  hipLaunchKernelGGL(k_add_right_weighted, dim3(grid_for((size_t)n * n, 256)),
-                     dim3(256), 0, st, g0inv, sigma, w, n);
+hipError_t launch_report(const int* status, int nmat, unsigned long long* keys, Report* rep,
+                         hipStream_t st) {
+  hipLaunchKernelGGL(k_report, dim3(1), dim3(256), 0, st, status, nmat, keys, rep);
   return hipGetLastError();
 }
 
-hipError_t launch_shifted_pair(const c64* g0inv, double d0, double d1, c64* x0,
-                               c64* x1, int ld, int n, hipStream_t st) {
-  hipLaunchKernelGGL(k_shifted_pair, dim3(grid_for((size_t)n * n, 256)),
-                     dim3(256), 0, st, g0inv, d0, d1, x0, x1, ld, n);
+hipError_t launch_right_weight(const c64* src0, c64* dst0, const c64* src1, c64* dst1,
+                               const c64* w, int n, hipStream_t st) {
+  hipLaunchKernelGGL(k_right_weight, dim3(grid_for((size_t)n * n, 256), 2), dim3(256), 0, st,
+                     src0, dst0, src1, dst1, w, n);
   return hipGetLastError();
 }
 
 hipError_t launch_sigma_fk(const c64* x, const c64* w, c64* sigma, int n, double h,
-                           double gam, unsigned long long* key, hipStream_t st) {
+                           double gam, const int* status, unsigned long long* key,
+                           hipStream_t st) {
   const int g = grid_for((size_t)n * n, 256);
   hipLaunchKernelGGL(k_sigma_fk, dim3(g > 2048 ? 2048 : g), dim3(256), 0, st, x, w,
-                     sigma, n, h, gam, key);
+                     sigma, n, h, gam, status, key);
   return hipGetLastError();
 }
 

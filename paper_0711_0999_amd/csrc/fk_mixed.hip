@@ -65,7 +65,7 @@ __global__ __launch_bounds__(256, 2) void k_bgemm(
 }
 
 // R = I - T X + P in place of P (P = Sigma_t X), T = i I + sub-diagonal tsub
-// + corner tcor at (0, n-1); running max |R| into key.
+// + corner tcor at (0, n-1); running max |R| into key (nullable).
 __global__ void k_residual(c64* __restrict__ P, const c64* __restrict__ X,
                            const c64* __restrict__ tsub,
                            const c64* __restrict__ tcor, int n, int nmat,
@@ -99,7 +99,7 @@ __global__ void k_residual(c64* __restrict__ P, const c64* __restrict__ X,
     const unsigned long long o = __shfl_xor(k, off);
     k = o > k ? o : k;
   }
-  if ((threadIdx.x & 63) == 0) atomicMax(key, k);
+  if (key && (threadIdx.x & 63) == 0) atomicMax(key, k);
 }
 
 template <typename TI>
