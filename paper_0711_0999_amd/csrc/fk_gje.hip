@@ -122,7 +122,7 @@ template <typename T, int KW> struct PivotRows {
 // the rows whose pivot column pcol lies in [jp, jp + w) masked.  Columns of
 // [skip, skip + w) inside the block are left alone (KW < 32: the eliminated
 // group inside its own quarter).
-// Each of NW waves takes 16 rows x 16 NH columns at a time and reads M and C straight
+// Each wave takes 16 rows x 32 columns at a time and reads M and C straight
 // from memory in the matrix cores' operand layouts, the next step's values in
 // flight while the current one is multiplied: nothing but B goes through LDS
 // and the waves never wait for each other (row tiles staged through LDS with
@@ -132,7 +132,7 @@ template <typename T, int KW> struct PivotRows {
 // products and before its stores, so that no load ever waits for a store.
 // FULL: w = KW and cw = 32 (no lane masks, loads that are always issued).
 // Products in the three-product form of the trailing update.
-template <typename T, int KW, int NW, int NH, bool FULL, typename V>
+template <typename T, int KW, int NW, bool FULL, typename V>
 __device__ __forceinline__ void block_update_as(const V& x, int m,
                              const int* __restrict__ pcol, int j0, int jp, int w,
                              int c0, int cw, int skip,
@@ -144,34 +144,33 @@ __device__ __forceinline__ void block_update_as(const V& x, int m,
   const int tid = fresh_tid();
   const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int li = lane & 15, lk = lane >> 4;
-  // unit u: row tile u / (2 / NH), NH 16-column halves from column cb(u) on
-  auto tile = [](int u) { return NH == 2 ? u : u >> 1; };
-  auto cb = [](int u) { return NH == 2 ? 0 : 16 * (u & 1); };
-  struct CTile {                                 // one unit's C and where it is
-    cplx<T> c[NH][4];
+  const bool in0 = FULL || li < cw, in1 = FULL || 16 + li < cw;
+  const bool st0 = in0 && !(KW < 32 && li >= skip && li < skip + w);
+  const bool st1 = in1 && !(KW < 32 && 16 + li >= skip && 16 + li < skip + w);
+  struct CTile {                                 // one tile's C and where it is
+    cplx<T> c[2][4];
     typename V::Ref at[4];
     int pc[4];
   };
-  auto load_c = [&](CTile& ct, int u) {
+  auto load_c = [&](CTile& ct, int t) {
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
-      const int e = min(16 * tile(u) + Mfma<T>::drow(lk, v), m - 1);
-      ct.at[v] = x.ref(e, c0 + cb(u) + li);
+      const int e = min(16 * t + Mfma<T>::drow(lk, v), m - 1);
+      ct.at[v] = x.ref(e, c0 + li);
       ct.pc[v] = pcol[e];
-#pragma unroll
-      for (int h = 0; h < NH; ++h) {
-        if (FULL) {
-          ct.c[h][v] = x.at(ct.at[v])[16 * h];
-        } else {
-          ct.c[h][v].re = ct.c[h][v].im = T(0);
-          if (cb(u) + 16 * h + li < cw) ct.c[h][v] = x.at(ct.at[v])[16 * h];
-        }
+      if (FULL) {
+        ct.c[0][v] = x.at(ct.at[v])[0];
+        ct.c[1][v] = x.at(ct.at[v])[16];
+      } else {
+        ct.c[0][v].re = ct.c[0][v].im = ct.c[1][v].re = ct.c[1][v].im = T(0);
+        if (in0) ct.c[0][v] = x.at(ct.at[v])[0];
+        if (in1) ct.c[1][v] = x.at(ct.at[v])[16];
       }
     }
   };
-  auto load_m = [&](cplx<T> (&mn)[KS], int u, int ch) {
+  auto load_m = [&](cplx<T> (&mn)[KS], int t, int ch) {
     const int k0 = 4 * KS * ch;
-    const cplx<T>* src = x.at(x.ref(min(16 * tile(u) + li, m - 1), j0 + k0 + lk));
+    const cplx<T>* src = x.at(x.ref(min(16 * t + li, m - 1), j0 + k0 + lk));
 #pragma unroll
     for (int s = 0; s < KS; ++s) {
       if (FULL) {
@@ -182,8 +181,8 @@ __device__ __forceinline__ void block_update_as(const V& x, int m,
       }
     }
   };
-  const int nu = ((m + 15) >> 4) * (2 / NH);
-  if (wave >= nu) return;
+  const int nt = (m + 15) >> 4;
+  if (wave >= nt) return;
   // a short product (KW < 32) has the next tile's C in flight too; a long one
   // covers the latency of its own C, which saves the registers
   constexpr bool kNextC = KW < 32;
@@ -192,41 +191,41 @@ __device__ __forceinline__ void block_update_as(const V& x, int m,
   load_m(a, wave, 0);
   if (kNextC) load_c(ct, wave);
 #pragma unroll 1
-  for (int u = wave; u < nu; u += NW) {
-    if (!kNextC) load_c(ct, u);
-    v4 p1[NH], p2[NH], p3[NH];
+  for (int t = wave; t < nt; t += NW) {
+    if (!kNextC) load_c(ct, t);
+    v4 p1[2], p2[2], p3[2];
 #pragma unroll
-    for (int h = 0; h < NH; ++h)
+    for (int h = 0; h < 2; ++h)
 #pragma unroll
       for (int v = 0; v < 4; ++v) p1[h][v] = p2[h][v] = p3[h][v] = T(0);
 #pragma unroll 1
     for (int ch = 0; ch < NCH; ++ch) {
-      cplx<T> b[2][NH];
-      T bsum[2][NH];
-      const int bo = (4 * ch * KS + lk) * kBP + cb(u) + li;
+      cplx<T> b[2][2];
+      T bsum[2][2];
+      const int bo = (4 * ch * KS + lk) * kBP + li;
 #pragma unroll
-      for (int h = 0; h < NH; ++h) {
+      for (int h = 0; h < 2; ++h) {
         b[0][h] = B.v[bo + 16 * h];
         bsum[0][h] = B.s[bo + 16 * h];
       }
       // the next step (past the last one: rows clamped, values unused)
-      if (ch + 1 < NCH) load_m(mn, u, ch + 1);
-      else load_m(mn, u + NW, 0);
-      if (kNextC) load_c(cn, u + NW);
+      if (ch + 1 < NCH) load_m(mn, t, ch + 1);
+      else load_m(mn, t + NW, 0);
+      if (kNextC) load_c(cn, t + NW);
 #pragma unroll
       for (int s = 0; s < KS; ++s) {
         // the next k-step's B is read during this one's products; the fence
         // keeps the scheduler from reading all of them at once (registers)
         if (s + 1 < KS) {
 #pragma unroll
-          for (int h = 0; h < NH; ++h) {
+          for (int h = 0; h < 2; ++h) {
             b[(s + 1) & 1][h] = B.v[bo + 4 * (s + 1) * kBP + 16 * h];
             bsum[(s + 1) & 1][h] = B.s[bo + 4 * (s + 1) * kBP + 16 * h];
           }
         }
         const T as = a[s].re + a[s].im;
 #pragma unroll
-        for (int h = 0; h < NH; ++h) {
+        for (int h = 0; h < 2; ++h) {
           const cplx<T> bb = b[s & 1][h];
           p1[h] = Mfma<T>::run(a[s].re, bb.re, p1[h]);
           p2[h] = Mfma<T>::run(a[s].im, bb.im, p2[h]);
@@ -239,7 +238,7 @@ __device__ __forceinline__ void block_update_as(const V& x, int m,
       for (int s = 0; s < KS; ++s) a[s] = mn[s];
     }
 #pragma unroll
-    for (int h = 0; h < NH; ++h)
+    for (int h = 0; h < 2; ++h)
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
         const bool keep = !(ct.pc[v] >= jp && ct.pc[v] < jp + w);
@@ -247,35 +246,33 @@ __device__ __forceinline__ void block_update_as(const V& x, int m,
         ct.c[h][v].re = (q1 - q2) + (keep ? ct.c[h][v].re : T(0));
         ct.c[h][v].im = ((p3[h][v] - q1) - q2) + (keep ? ct.c[h][v].im : T(0));
       }
-    const bool whole = FULL && 16 * tile(u) + 16 <= m;
+    if (FULL && 16 * t + 16 <= m) {
 #pragma unroll
-    for (int h = 0; h < NH; ++h) {
-      const int col = cb(u) + 16 * h + li;
-      const bool st = (FULL || col < cw) && !(KW < 32 && col >= skip && col < skip + w);
-      if (whole) {
-        if (KW >= 32 || st) {
+      for (int h = 0; h < 2; ++h)
+        if (KW >= 32 || (h ? st1 : st0)) {
 #pragma unroll
           for (int v = 0; v < 4; ++v) x.at(ct.at[v])[16 * h] = ct.c[h][v];
         }
-      } else {
+    } else {
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
 #pragma unroll
         for (int v = 0; v < 4; ++v)
-          if (st && 16 * tile(u) + Mfma<T>::drow(lk, v) < m)
+          if ((h ? st1 : st0) && 16 * t + Mfma<T>::drow(lk, v) < m)
             x.at(ct.at[v])[16 * h] = ct.c[h][v];
-      }
     }
     if (kNextC) ct = cn;
   }
 }
-template <typename T, int KW, int NW, int NH, typename V>
+template <typename T, int KW, int NW = kPW, typename V>
 __device__ __forceinline__ void block_update(const V& x, int m,
                              const int* __restrict__ pcol, int j0, int jp, int w,
                              int c0, int cw, int skip,
                              const PivotRows<T, kNB>& B) {
   if (w == KW && cw == 32)
-    block_update_as<T, KW, NW, NH, true>(x, m, pcol, j0, jp, w, c0, cw, skip, B);
+    block_update_as<T, KW, NW, true>(x, m, pcol, j0, jp, w, c0, cw, skip, B);
   else
-    block_update_as<T, KW, NW, NH, false>(x, m, pcol, j0, jp, w, c0, cw, skip, B);
+    block_update_as<T, KW, NW, false>(x, m, pcol, j0, jp, w, c0, cw, skip, B);
 }
 
 // B of block_update: row l, column c = value of list entry pive[l] (the pivot
@@ -446,10 +443,10 @@ __device__ __forceinline__ void eliminate_columns(const V& x, const int* rows, i
     __syncthreads();
     if (!any) continue;
     // ---- the block's pivot, from the kPW candidates
-    static_assert(kPW == 8, "candidates");
-    const int* ck = cd.key[par];
-    const int gmax = __builtin_amdgcn_readfirstlane(
-        max(max(max(ck[0], ck[1]), max(ck[2], ck[3])), max(max(ck[4], ck[5]), max(ck[6], ck[7]))));
+    int gmax = cd.key[par][0];
+#pragma unroll
+    for (int q = 1; q < kPW; ++q) gmax = max(gmax, cd.key[par][q]);
+    gmax = __builtin_amdgcn_readfirstlane(gmax);
     // a valid unpivoted entry: the list holds at least as many rows as this
     // block has columns
     const int pe = kPlace - (gmax & kPlace);
@@ -462,8 +459,12 @@ __device__ __forceinline__ void eliminate_columns(const V& x, const int* rows, i
     inv.re = prow[0].re * den;
     inv.im = -prow[0].im * den;
     const bool mine = (pe & (kPanelThreads - 1)) == tid;
-    if (tid == 0) {      // (the rest of the bookkeeping follows the group)
-      pive[l] = min(pe, m - 1);
+    if (mine) {
+      const int e = min(pe, m - 1), p = rows[e];
+      piv[ca + l] = p;
+      rowcol[p] = ca + l;
+      pcol[e] = ca + l;
+      pive[l] = e;
       const bool zero = prow[0].re == T(0) && prow[0].im == T(0);
       if (zero || gmax >= (bad_key<T>() & ~kPlace))
         atomicCAS(status, 0, zero ? (1 + ca + l) : -(1 + ca + l));
@@ -519,12 +520,6 @@ __device__ __forceinline__ void eliminate_columns(const V& x, const int* rows, i
       v[i][IB - 1] = f;
     }
   if (any) store_group<T, RPT, IB>(x, m, c, iw, tid, stage, v);
-  if (tid < iw) {        // pive: written by this wave
-    const int e = pive[tid], p = rows[e];
-    piv[ca + tid] = p;
-    rowcol[p] = ca + tid;
-    pcol[e] = ca + tid;
-  }
 }
 
 // Outer block S of one matrix.  Rows pivoted in earlier blocks take no part:
@@ -600,15 +595,13 @@ __global__ __launch_bounds__(kPanelThreads, 1) void k_outer_panel(
   }
 
   const int J1 = J0 + kNB;
-  // a dozen row tiles spread more evenly over the waves by halves
-  constexpr int NH = QR > 0 && QR <= 192 ? 1 : 2;
   const InMemory<T> x{xbuf + d.xoff, roff};
   // update the columns [c0, c0 + cw) with the transform of [j0, j0 + w); the
   // barriers order it after the writes before it and before the reads after
   auto cross32 = [&](int j0, int w, int c0, int cw) {
     load_pivot_rows<T, 32>(x, pive + (j0 - J0), w, c0, cw, -1, B);
     __syncthreads();
-    block_update<T, 32, kPW, NH>(x, m, pcol, j0, j0, w, c0, cw, 0, B);
+    block_update<T, 32>(x, m, pcol, j0, j0, w, c0, cw, 0, B);
     __syncthreads();
   };
   auto cross64 = [&](int j0, int w, int c0) {
@@ -616,7 +609,7 @@ __global__ __launch_bounds__(kPanelThreads, 1) void k_outer_panel(
     for (int c = c0; c < min(c0 + kNB, n); c += 32) {
       load_pivot_rows<T, kNB>(x, pive + (j0 - J0), w, c, min(32, n - c), -1, B);
       __syncthreads();
-      block_update<T, kNB, kPW, NH>(x, m, pcol, j0, j0, w, c, min(32, n - c), 0, B);
+      block_update<T, kNB>(x, m, pcol, j0, j0, w, c, min(32, n - c), 0, B);
       __syncthreads();
     }
   };
@@ -632,7 +625,7 @@ __global__ __launch_bounds__(kPanelThreads, 1) void k_outer_panel(
       if (cw > IB) {
         load_pivot_rows<T, IB>(view, pe, iw, f, cw, b0, B);
         __syncthreads();
-        block_update<T, IB, kPW, NH>(view, m, pcol, f + b0, c0 + b0, iw, f, cw, b0, B);
+        block_update<T, IB>(view, m, pcol, f + b0, c0 + b0, iw, f, cw, b0, B);
         __syncthreads();
       }
     }
@@ -729,7 +722,7 @@ __global__ __launch_bounds__(256, 2) void k_cross(
   const int m = count;
   if (m == 0) return;
   const InMemory<T> x{xbuf + d.xoff, roff};
-  block_update<T, KW, 4, 2>(x, m, pcol, j0, j0, w, c0, cw, 0, B);
+  block_update<T, KW, 4>(x, m, pcol, j0, j0, w, c0, cw, 0, B);
 }
 
 // ------------------------------------------------------------------ gather
