@@ -240,3 +240,11 @@ def test_gradient_shapes(lib, d_in, width, depth, d_out, rows):
     assert abs(loss - lo) < 1e-5 * lo
     assert relerr(g, go) < 1e-4
     net.close()
+
+
+@pytest.mark.parametrize("d_in,width,rows", [
+    (96, 512, 1), (96, 512, 63), (96, 512, 65),   # edges of a block of 64 rows
+    (40, 384, 65), (576, 128, 193),               # ragged input; widest input
+])
+def test_bf16_forward_block_edges(lib, d_in, width, rows):
+    test_bf16_forward_shapes(lib, d_in, width, 3, 2, rows)
