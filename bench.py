@@ -42,7 +42,7 @@ PEAK_HBM_GBS = 8000.0
 # Measured: FETCH_SIZE 69358020 KiB x 2.00 + WRITE_SIZE 26671992 KiB x 1.00
 # per launch.
 PROFILED_TRAFFIC = {"kernel": "fk::k_update<double, 2>", "batch": 757,
-                    "bytes_per_launch": (2.00 * 69358019.7 + 1.00 * 26671992.2) * 1024}
+                    "bytes_per_launch": (2.00 * 72949560.0 + 1.00 * 30007057.0) * 1024}
 
 # Each complex product of the trailing update is formed from three real ones
 # (Gauss), so its matrix cores execute 6 of the 8 real flops per complex

@@ -195,8 +195,9 @@ fk_status fk_wigner_dos(const fk_ctx* ctx, int n_T, const int* t_index, int n_w,
  * graph capture, tight serving loops, harnesses that forbid hipMalloc): the
  * same arguments, result and errors, but the time indices, frequencies and
  * result are staged through a 4 MiB static device array of the library (one
- * per GPU, set up by fk_create, held until the process ends) instead of a
- * per-call allocation; no hipMalloc, hipFree or allocating library call.
+ * per GPU, set up by fk_create, held until the process ends) instead of memory
+ * that the call may have to allocate; no hipMalloc, hipFree or allocating
+ * library call.
  * 256-byte-aligned segments of 4 n_T + 8 n_w + 8 n_T n_w bytes must fit in
  * 4 MiB, else FK_EINVAL (e.g. 100 times x 5000 frequencies fit).  All calls on
  * one GPU share the array: calls that overlap in time on the same GPU (other
