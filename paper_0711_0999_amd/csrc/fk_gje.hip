@@ -534,14 +534,18 @@ __device__ __forceinline__ void eliminate_columns(const V& x, const int* rows, i
 // One matrix of N_c = 1800: 1359 -> 695 us per block on average over the
 // blocks; 100 matrices of N_c = 150: 370 -> 130 us; 225 of N_c = 1800: 1636 ->
 // 1250 us, where the quarters' passes are bound by memory traffic.
-// SPLIT: only quarter `only`, on the same rows; the joins are launches of
-// k_cross, for which the quarter's pivot rows are copied aside.
-template <typename T, int RPT, int IB, int QR, bool SPLIT>
+// kQuarters: only quarter `only`, on the same rows; the joins are launches of
+// k_cross, for which the quarter's pivot rows are copied aside.  kGroups: only
+// group `only`; its update of the quarter's other columns is such a launch too.
+enum PanelForm { kWhole, kQuarters, kGroups };
+template <typename T, int RPT, int IB, int QR, PanelForm FORM>
 __global__ __launch_bounds__(kPanelThreads, 1) void k_outer_panel(
     cplx<T>* __restrict__ xbuf, int* __restrict__ pivbuf,
     int* __restrict__ rowcolbuf, const MatDesc* __restrict__ descs, int S,
     int* __restrict__ status, int only, cplx<T>* __restrict__ side) {
   constexpr int kCap = QR > 0 ? QR : RPT * kPanelThreads;
+  constexpr bool SPLIT = FORM != kWhole;
+  constexpr int kPart = FORM == kGroups ? IB : 32;   // columns of part `only`
   static_assert(kCap <= RPT * kPanelThreads, "panel rows");
   __shared__ PivotRows<T, kNB> B;
   __shared__ Candidates<T, IB> cd;
@@ -555,7 +559,7 @@ __global__ __launch_bounds__(kPanelThreads, 1) void k_outer_panel(
   const MatDesc d = descs[blockIdx.x];
   const int n = d.n;
   const int J0 = S * kNBO;
-  if (J0 >= n || (SPLIT && J0 + 32 * only >= n)) return;
+  if (J0 >= n || (SPLIT && J0 + kPart * only >= n)) return;
   int* piv = pivbuf + d.ioff;
   int* rowcol = rowcolbuf + d.ioff;
   int* st = status + d.status_idx;
@@ -641,8 +645,12 @@ __global__ __launch_bounds__(kPanelThreads, 1) void k_outer_panel(
     __syncthreads();
   };
   if constexpr (SPLIT) {
-    const int c0 = J0 + 32 * only, cw = min(32, n - c0);
-    if constexpr (QR > 0) {
+    const int c0 = J0 + kPart * only, cw = min(kPart, n - c0);
+    if constexpr (FORM == kGroups) {
+      eliminate_columns<T, RPT, IB, kCap>(x, rows, m, c0, c0, cw, place, piv, rowcol, pcol,
+                                          pive + (c0 - J0), st, stage, cd);
+      __syncthreads();
+    } else if constexpr (QR > 0) {
       copy_quarter(c0, cw, false);
       quarter(InLds<T>{stage}, 0, c0, cw);
       copy_quarter(c0, cw, true);
@@ -683,7 +691,8 @@ __global__ __launch_bounds__(kPanelThreads, 1) void k_outer_panel(
 // Join of a split panel's parts: the columns [co, co + 32 gridDim.z) of block S
 // receive the transform of its KW columns from jo on (offsets in the block) on
 // all rows not pivoted before the block, 64 rows per workgroup; B was copied
-// aside by the quarters' launches.
+// aside by the parts' launches.  KW < 32: a group inside its own quarter, whose
+// columns it leaves alone.
 template <typename T, int KW>
 __global__ __launch_bounds__(256, 2) void k_cross(
     cplx<T>* __restrict__ xbuf, const int* __restrict__ rowcolbuf,
@@ -722,7 +731,7 @@ __global__ __launch_bounds__(256, 2) void k_cross(
   const int m = count;
   if (m == 0) return;
   const InMemory<T> x{xbuf + d.xoff, roff};
-  block_update<T, KW, 4>(x, m, pcol, j0, j0, w, c0, cw, 0, B);
+  block_update<T, KW, 4>(x, m, pcol, j0, j0, w, c0, cw, KW < 32 ? jo - cz : 0, B);
 }
 
 // ------------------------------------------------------------------ gather
@@ -954,25 +963,23 @@ hipError_t gje_panel(cplx<T>* x, int* piv, int* rowcol, const MatDesc* d,
   // by the rows left: quarters of at most 192 (complex64 448) rows stay in
   // LDS; then one, two or four rows per thread; beyond 2048 rows four columns
   // per register block keep the rows in registers
-  auto go = [&](auto split, int only) {
-    constexpr bool SP = decltype(split)::value;
-    auto one = [&](auto kernel) {
-      hipLaunchKernelGGL(kernel, dim3(nmat), dim3(kPanelThreads), 0, st, x, piv, rowcol, d,
-                         S, status, only, side);
-      ++*launches;
-    };
-    if (left <= 192) one(k_outer_panel<T, 1, kIB, 192, SP>);
-    else if (left <= 448 && sizeof(T) == 4) one(k_outer_panel<T, 1, kIB, sizeof(T) == 4 ? 448 : 0, SP>);
-    else if (left <= kPanelThreads) one(k_outer_panel<T, 1, kIB, 0, SP>);
-    else if (left <= 2 * kPanelThreads) one(k_outer_panel<T, 2, kIB, 0, SP>);
-    else if (left <= 4 * kPanelThreads) one(k_outer_panel<T, 4, kIB, 0, SP>);
-    else if (left <= 6 * kPanelThreads) one(k_outer_panel<T, 6, 4, 0, SP>);
-    else one(k_outer_panel<T, kMaxN / kPanelThreads, 4, 0, SP>);
+  auto one = [&](auto kernel, int only) {
+    hipLaunchKernelGGL(kernel, dim3(nmat), dim3(kPanelThreads), 0, st, x, piv, rowcol, d, S,
+                       status, only, side);
+    ++*launches;
   };
+  constexpr int kC64 = sizeof(T) == 4 ? 448 : 0;
+  constexpr int kMany = kMaxN / kPanelThreads;
   // few matrices leave most CUs idle while one CU each joins the panel's
   // parts: the joins then run as launches over all row tiles
   if (!side || nmat > kSplitMats || left <= kSplitRows) {
-    go(std::false_type{}, 0);
+    if (left <= 192) one(k_outer_panel<T, 1, kIB, 192, kWhole>, 0);
+    else if (left <= kC64) one(k_outer_panel<T, 1, kIB, kC64, kWhole>, 0);
+    else if (left <= kPanelThreads) one(k_outer_panel<T, 1, kIB, 0, kWhole>, 0);
+    else if (left <= 2 * kPanelThreads) one(k_outer_panel<T, 2, kIB, 0, kWhole>, 0);
+    else if (left <= 4 * kPanelThreads) one(k_outer_panel<T, 4, kIB, 0, kWhole>, 0);
+    else if (left <= 6 * kPanelThreads) one(k_outer_panel<T, 6, 4, 0, kWhole>, 0);
+    else one(k_outer_panel<T, kMany, 4, 0, kWhole>, 0);
     return hipGetLastError();
   }
   auto cross = [&](auto kernel, int jo, int co, int nz) {
@@ -981,12 +988,39 @@ hipError_t gje_panel(cplx<T>* x, int* piv, int* rowcol, const MatDesc* d,
                        side, d, S, jo, co);
     ++*launches;
   };
+  // With more than 512 rows the groups' updates of a quarter too are launches
+  // over all row tiles: one CU would move the quarter through memory once per
+  // group.  One matrix of N_c = 1800 10.6 -> 9.1 ms per impurity update, 25 of
+  // N_c = 4100 224 -> 215 ms.  Beyond 1024 rows level at 64 matrices and faster
+  // with fewer; from 513 to 1024 rows the launches cost more than they save
+  // above kGroupMats (N_c = 1000: 16 matrices 5.36 -> 5.07 ms, 32 7.46 -> 7.35,
+  // 48 9.65 both, 64 11.7 -> 11.9); up to 512 rows no difference.
+  auto groups = [&](auto kernel, auto join, int ib, int o) {
+    for (int g = o; g < std::min(o + 32, left); g += ib) {
+      one(kernel, g / ib);
+      cross(join, g, o, 1);
+    }
+  };
+  auto quarter = [&](int o) {
+    const int q = o / 32;
+    if (left <= kC64) one(k_outer_panel<T, 1, kIB, kC64, kQuarters>, q);
+    else if (left <= kPanelThreads) one(k_outer_panel<T, 1, kIB, 0, kQuarters>, q);
+    else if (left <= 2 * kPanelThreads && nmat > kGroupMats)
+      one(k_outer_panel<T, 2, kIB, 0, kQuarters>, q);
+    else if (left <= 2 * kPanelThreads)
+      groups(k_outer_panel<T, 2, kIB, 0, kGroups>, k_cross<T, kIB>, kIB, o);
+    else if (left <= 4 * kPanelThreads)
+      groups(k_outer_panel<T, 4, kIB, 0, kGroups>, k_cross<T, kIB>, kIB, o);
+    else if (left <= 6 * kPanelThreads)
+      groups(k_outer_panel<T, 6, 4, 0, kGroups>, k_cross<T, 4>, 4, o);
+    else groups(k_outer_panel<T, kMany, 4, 0, kGroups>, k_cross<T, 4>, 4, o);
+  };
   for (int h = 0; h < 2; ++h) {
     const int o = kNB * h;
     if (o >= left) break;
-    go(std::true_type{}, 2 * h);
+    quarter(o);
     cross(k_cross<T, 32>, o, o + 32, 1);
-    if (o + 32 < left) go(std::true_type{}, 2 * h + 1);
+    if (o + 32 < left) quarter(o + 32);
     cross(k_cross<T, 32>, o + 32, o, 1);
     cross(k_cross<T, kNB>, o, kNB - o, 2);
   }

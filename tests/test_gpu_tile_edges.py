@@ -103,3 +103,26 @@ def test_split_panels_equal_whole_ones(lib, n_c):
                 ctx.compute_gloc(precision)
                 got.append(ctx.get_gloc())
             assert relerr(got[1], got[0]) < bar
+
+
+def test_split_panels_of_many_rows_equal_whole_ones(lib):
+    """The largest rows-per-thread form, whose split panels are launches per
+    group of columns."""
+    test_split_panels_equal_whole_ones(lib, 3073)
+
+
+def test_split_panels_of_uneven_matrices(lib):
+    """A few uneven matrices in one batch: small ones end inside a quarter and
+    inside a group of columns of a panel that the largest one splits by groups."""
+    sizes = (1155, 140, 170, 129)
+    print(f"case: uneven split panels, N_c = {sizes}", flush=True)
+    inst = [dict(U=1.0, E=1.5, n_eps=1, n_ebar=2, **contour(n)) for n in sizes]
+    sig = [inputs.random_sigma(n, seed=n, scale=0.1) for n in sizes]
+    with lib.Batch(inst) as b:
+        for i, s in enumerate(sig):
+            b.instance(i).set_sigma(s)
+        b.iterate(1, 0.0)
+        for i, n in enumerate(sizes):
+            go, jo = lattice(contour(n), sig[i], 1, 2)
+            assert relerr(b.instance(i).get_gloc(), go) < 1e-10
+            assert relerr(b.instance(i).get_current()[1], jo) < 1e-10
