@@ -57,9 +57,10 @@ constexpr int kPanelThreads = 512;
 constexpr int kGemmThreads = 256;
 // Panels of at most kSplitMats matrices are split into launches while more
 // than kSplitRows rows are left: one matrix of N_c = 1800 14.4 -> 10.7 ms per
-// impurity update, 25 of N_c = 4100 242.6 -> 225.2 ms per step (9.1 and 214 with
-// the groups' updates as launches too), 64 complex64 ones of N_c = 600 no change; 225 of N_c = 751 would lose 5%, and a quarter
-// that stays in LDS is too short for ten launches.
+// impurity update, 25 of N_c = 4100 242.6 -> 225.2 ms per step (9.1 and 214
+// with the groups' updates as launches too), 64 complex64 ones of N_c = 600 no
+// change; 225 of N_c = 751 would lose 5%, and a quarter that stays in LDS is
+// too short for ten launches.
 constexpr int kSplitMats = 64;
 constexpr int kSplitRows = 192;
 constexpr int kGroupMats = 32;   // see gje_panel
