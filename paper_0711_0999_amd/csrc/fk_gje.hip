@@ -33,6 +33,9 @@
 #include "fk_internal.h"
 #include "fk_tile.h"
 
+#include <climits>
+#include <limits>
+
 namespace fk {
 
 template <typename T>
@@ -47,25 +50,25 @@ constexpr int kPW = kPanelThreads / 64;          // waves of the panel kernel
 constexpr int kBP = 33;                          // LDS row of a 32-column block
 static_assert(kNBO == 2 * kNB && kTile == kNB, "block sizes");
 
-// Pivot key of a candidate z, an int that orders like |re| + |im|: the float's
-// bits, or the double's upper word.  Infinities and NaN order above every
-// number (bad_key).
-__device__ __forceinline__ int pivot_key(const c64& z) {
-  return (int)(__double_as_longlong(fabs(z.re) + fabs(z.im)) >> 32);
+// Pivot key of a candidate z: the bits of |re| + |im| as a signed integer, which
+// orders like the value itself; infinities and NaN order above every number.
+// The top bit of `taken` puts pivoted and absent rows below all of them.
+template <typename T> struct KeyOf;
+template <> struct KeyOf<double> { typedef long long type; };
+template <> struct KeyOf<float> { typedef int type; };
+__device__ __forceinline__ long long pivot_key(const c64& z, unsigned taken) {
+  const long long b = __double_as_longlong(fabs(z.re) + fabs(z.im));
+  const unsigned hi = ((unsigned)(b >> 32) & 0x7fffffffu) | (taken & 0x80000000u);
+  return (long long)(((unsigned long long)hi << 32) | (unsigned)b);
 }
-__device__ __forceinline__ int pivot_key(const c32& z) {
-  return __float_as_int(fabsf(z.re) + fabsf(z.im));
+__device__ __forceinline__ int pivot_key(const c32& z, unsigned taken) {
+  return (int)((__float_as_uint(fabsf(z.re) + fabsf(z.im)) & 0x7fffffffu) |
+               (taken & 0x80000000u));
 }
-template <typename T> __device__ __forceinline__ constexpr int bad_key() {
-  return sizeof(T) == 8 ? 0x7ff00000 : 0x7f800000;
-}
-// Low bits of a key that carry the candidate's place in the row list (counted
-// down, so that among equal keys the lowest row wins) for lists of up to cap.
-constexpr int place_mask(int cap) {
-  int b = 1;
-  while (b < cap) b *= 2;
-  return b - 1;
-}
+__device__ __forceinline__ int key_hi(long long k) { return (int)(k >> 32); }
+__device__ __forceinline__ int key_hi(int k) { return k; }
+__device__ __forceinline__ int key_lo(long long k) { return (int)((unsigned)k ^ 0x80000000u); }
+__device__ __forceinline__ int key_lo(int) { return 0; }
 
 // Maxima over lanes through the ALU's DPP paths (an LDS permute per step would
 // cost about 100 cycles of latency in a chain of six).
@@ -80,6 +83,32 @@ __device__ __forceinline__ int max_of_wave(int x) {    // uniform
   x = dpp_max<0x142, 0xa>(x);          // row_bcast 15 into rows 1 and 3
   x = dpp_max<0x143, 0xc>(x);          // row_bcast 31 into rows 2 and 3
   return __builtin_amdgcn_readlane(x, 63);
+}
+
+__device__ __forceinline__ unsigned long long ballot(bool b) {
+  return __builtin_amdgcn_ballot_w64(b);
+}
+// Of the lanes in `mask`, which share the upper word of their keys, those with
+// the largest key (FP64: one more maximum, over the lower words).
+template <typename K>
+__device__ __forceinline__ unsigned long long largest_of(unsigned long long mask, K key) {
+  if (sizeof(K) == 8 && (mask & (mask - 1)) != 0) {
+    const bool in = (mask >> (threadIdx.x & 63)) & 1;
+    const int lo = in ? key_lo(key) : INT_MIN;
+    const int top = max_of_wave(lo);
+    mask = ballot(in && lo == top);
+  }
+  return mask;
+}
+
+// Of the lanes in `mask`, those whose `slot` (below N) is the smallest.
+template <int N>
+__device__ __forceinline__ unsigned long long first_slot(unsigned long long mask, int slot) {
+  const bool in = (mask >> (threadIdx.x & 63)) & 1;
+  unsigned long long s = 0;
+#pragma unroll 1
+  for (int i = 0; i < N && s == 0; ++i) s = ballot(in && slot == i);
+  return s;
 }
 
 // This thread's index, opaque to the optimizer: what a panel step derives from
@@ -297,12 +326,13 @@ __device__ __forceinline__ void load_pivot_rows(const V& x, const int* pive, int
 }
 
 // -------------------------------------------------- panel: column elimination
-// LDS of one group's pivot search: each wave's candidate (key with place, and
+// LDS of one group's pivot search: each wave's candidate (key, place and
 // the row's values), double-buffered by column parity so that one column's
 // reads never meet the next column's writes.
 template <typename T, int IB> struct Candidates {
   cplx<T> row[2][kPW][IB];
-  int key[2][kPW];
+  int hi[2][kPW];      // upper word of the key
+  int entry[2][kPW];   // the candidate's place in the row list
 };
 
 // The group's IB columns of the thread's rows, loaded and stored with the
@@ -387,14 +417,17 @@ __device__ __forceinline__ void store_group(const InLds<T>& x, int m, int c, int
   }
 }
 
-// Eliminate IB columns in registers on the m <= CAP listed rows, with partial
+// Eliminate IB columns in registers on the m listed rows, with partial
 // pivoting; thread tid owns list entries tid + i kPanelThreads, i < RPT, and
-// place[i] counts them down (-1 once that entry is pivoted, or if absent).
+// bit i of `taken` is set once that entry is pivoted, or if absent.
 // The columns are c .. in the frame of x and ca .. of the matrix.
-// A key holds the upper bits of |re| + |im| and the row's place, so that one
-// integer maximum yields the pivot and where it is; it leaves at least 7
-// mantissa bits (9 up to 2048 rows, 11 up to 512), which bounds the
-// multipliers by 1 + 2^-7 instead of 1, and equal keys go to the lowest row.
+// The pivot is the largest |re| + |im| of the rows left, compared in full; among
+// equal ones the lowest row.  So a row's |re| + |im| is at most the pivot's, and
+// a multiplier's modulus at most sqrt(2).  One integer maximum over the keys'
+// upper words finds the pivot but for ties, which the lower words (FP64) and then
+// the rows' order settle off the common path.  (A maximum over keys cut to 7 to
+// 11 mantissa bits, their low bits the row's place, took pivots up to 1 / 128
+// below the largest; impurity_1800 9.16 ms as here, loop_150 8.15 -> 8.21 ms.)
 // One barrier per column: every wave publishes its best candidate together
 // with the candidate's row, so that the row is in LDS when the winner is
 // known.  The chain per column bounds it (maximum over the wave's lanes,
@@ -404,56 +437,89 @@ __device__ __forceinline__ void store_group(const InLds<T>& x, int m, int c, int
 // The column loop is not unrolled: each step writes a row's columns one slot
 // down as it updates them, so that the column to eliminate is always slot 0
 // (the row is back in order after IB steps).
-template <typename T, int RPT, int IB, int CAP, typename V>
+template <typename T, int RPT, int IB, typename V>
 __device__ __forceinline__ void eliminate_columns(const V& x, const int* rows, int m,
-                             int c, int ca, int iw, int (&place)[RPT],
+                             int c, int ca, int iw, unsigned& taken,
                              int* __restrict__ piv, int* __restrict__ rowcol, int* pcol,
                              int* pive, int* __restrict__ status, cplx<T>* stage,
                              Candidates<T, IB>& cd) {
-  constexpr int kPlace = place_mask(CAP);
+  typedef typename KeyOf<T>::type K;
   const int tid = fresh_tid(), lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const bool any = wave * 64 < m;                // this wave holds rows
   cplx<T> v[RPT][IB];
   if (any) load_group<T, RPT, IB>(x, m, c, iw, tid, stage, v);
-  else if (lane == 0) cd.key[0][wave] = cd.key[1][wave] = -1;
+  else if (lane == 0) cd.hi[0][wave] = cd.hi[1][wave] = INT_MIN;
+  // this thread's largest key and the row that holds it (the first of equal ones)
+  K best;
+  int slot;
   auto thread_best = [&]() {
-    int b = -1;
+    best = pivot_key(v[0][0], taken << 31);
+    slot = 0;
 #pragma unroll
-    for (int i = 0; i < RPT; ++i)
-      b = max(b, (pivot_key(v[i][0]) & ~kPlace) | place[i]);
-    return b;
+    for (int i = 1; i < RPT; ++i) {
+      const K k = pivot_key(v[i][0], taken << (31 - i));
+      if (k > best) {
+        best = k;
+        slot = i;
+      }
+    }
   };
-  int best = thread_best(), wmax = any ? max_of_wave(best) : -1;
+  thread_best();
+  int wmax = any ? max_of_wave(key_hi(best)) : INT_MIN;
 #pragma unroll 1
   for (int l = 0; l < iw; ++l) {
     const int par = l & 1;
     if (any) {
-      if (wmax >= 0 ? best == wmax : lane == 0) {      // one lane
-        cd.key[par][wave] = wmax;
-        const int wi = (kPlace - (wmax & kPlace)) / kPanelThreads;   // uniform
+      auto publish = [&]() {
+        cd.hi[par][wave] = wmax;
+        cd.entry[par][wave] = tid + slot * kPanelThreads;
 #pragma unroll
         for (int i = 0; i < RPT; ++i)
-          if (i == wi) {
+          if (RPT == 1 || i == slot) {
 #pragma unroll
             for (int q = 0; q < IB; ++q) cd.row[par][wave][q] = v[i][q];
           }
+      };
+      const bool lead = key_hi(best) == wmax;
+      unsigned long long top = ballot(lead);
+      if (lead) publish();
+      if (__builtin_expect((top & (top - 1)) != 0, 0)) {
+        // several lanes wrote to the one place: the right one writes again
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        top = largest_of(top, best);
+        if (RPT > 1) top = first_slot<RPT>(top, slot);
+        if (lane == __builtin_ctzll(top)) publish();
       }
     }
     __syncthreads();
     if (!any) continue;
     // ---- the block's pivot, from the kPW candidates
-    int gmax = cd.key[par][0];
+    int gmax = cd.hi[par][0];
 #pragma unroll
-    for (int q = 1; q < kPW; ++q) gmax = max(gmax, cd.key[par][q]);
-    gmax = __builtin_amdgcn_readfirstlane(gmax);
-    // a valid unpivoted entry: the list holds at least as many rows as this
-    // block has columns
-    const int pe = kPlace - (gmax & kPlace);
-    const int win = (pe & (kPanelThreads - 1)) >> 6, pi = pe / kPanelThreads;
+    for (int q = 1; q < kPW; ++q) gmax = max(gmax, cd.hi[par][q]);
+    const int w8 = lane & (kPW - 1);
+    constexpr unsigned long long kWaves = (1ull << kPW) - 1;
+    unsigned long long top = ballot(cd.hi[par][w8] == gmax) & kWaves;
     cplx<T> prow[IB];
+    int pe;   // its list entry
+    auto take = [&]() {
+      const int win = __builtin_ctzll(top);
+      pe = cd.entry[par][win];
 #pragma unroll
-    for (int q = 0; q < IB; ++q) prow[q] = cd.row[par][win][q];
+      for (int q = 0; q < IB; ++q) prow[q] = cd.row[par][win][q];
+    };
+    take();
+    if (__builtin_expect((top & (top - 1)) != 0, 0)) {
+      top = largest_of(top, pivot_key(cd.row[par][w8][0], 0u));
+      if (RPT > 1 && (top & (top - 1)) != 0) {
+        const int e = (top >> lane) & 1 ? -cd.entry[par][w8] : INT_MIN;
+        const int first = max_of_wave(e);
+        top = ballot(e == first);
+      }
+      take();
+    }
+    const int pi = pe / kPanelThreads;
     // two divisions, not products with 1 / den: that overflows where den is
     // below the smallest normal number while the quotients do not (lattice_150
     // 502 -> 504 us, impurity_1800 9.10 -> 9.16 ms)
@@ -468,9 +534,9 @@ __device__ __forceinline__ void eliminate_columns(const V& x, const int* rows, i
       rowcol[p] = ca + l;
       pcol[e] = ca + l;
       pive[l] = e;
-      const bool zero = prow[0].re == T(0) && prow[0].im == T(0);
-      if (zero || gmax >= (bad_key<T>() & ~kPlace))
-        atomicCAS(status, 0, zero ? (1 + ca + l) : -(1 + ca + l));
+      const T size = fabs(prow[0].re) + fabs(prow[0].im);
+      if (__builtin_expect(!(size > T(0) && size < std::numeric_limits<T>::max()), 0))
+        atomicCAS(status, 0, size == T(0) ? (1 + ca + l) : -(1 + ca + l));
     }
     // ---- eliminate the column from every other row (Gauss-Jordan): row <-
     // row - t prow with t = row[0] / pivot and -t in this column's place.  The
@@ -487,7 +553,7 @@ __device__ __forceinline__ void eliminate_columns(const V& x, const int* rows, i
     for (int i = 0; i < RPT; ++i) {
       t[i] = cmul(v[i][0], inv);
       if (mine && i == pi) {
-        place[i] = -1;
+        taken |= 1u << i;
         t[i].re = -inv.re;
         t[i].im = -inv.im;
 #pragma unroll
@@ -501,8 +567,8 @@ __device__ __forceinline__ void eliminate_columns(const V& x, const int* rows, i
         v[i][IB - 1].im = -t[i].im;
       }
     }
-    best = thread_best();
-    wmax = max_of_wave(best);
+    thread_best();
+    wmax = max_of_wave(key_hi(best));
     if (kOverlap) {
 #pragma unroll
       for (int i = 0; i < RPT; ++i) {
@@ -594,11 +660,12 @@ __global__ __launch_bounds__(kPanelThreads, 1) void k_outer_panel(
   __syncthreads();
   if (m == 0) return;   // the same for every thread
 
-  int place[RPT];                // see eliminate_columns
+  unsigned taken = 0;            // see eliminate_columns
+  static_assert(RPT <= 32, "bits");
 #pragma unroll
   for (int i = 0; i < RPT; ++i) {
     const int e = tid + i * kPanelThreads;
-    place[i] = e < m && (!SPLIT || pcol[e] < 0) ? place_mask(kCap) - e : -1;
+    if (!(e < m && (!SPLIT || pcol[e] < 0))) taken |= 1u << i;
   }
 
   const int J1 = J0 + kNB;
@@ -626,7 +693,7 @@ __global__ __launch_bounds__(kPanelThreads, 1) void k_outer_panel(
     for (int b0 = 0; b0 < cw; b0 += IB) {
       const int iw = min(IB, cw - b0);
       int* pe = pive + (c0 - J0) + b0;
-      eliminate_columns<T, RPT, IB, kCap>(view, rows, m, f + b0, c0 + b0, iw, place, piv,
+      eliminate_columns<T, RPT, IB>(view, rows, m, f + b0, c0 + b0, iw, taken, piv,
                                           rowcol, pcol, pe, st, stage, cd);
       __syncthreads();   // pive, pcol and the eliminated columns
       if (cw > IB) {
@@ -650,7 +717,7 @@ __global__ __launch_bounds__(kPanelThreads, 1) void k_outer_panel(
   if constexpr (SPLIT) {
     const int c0 = J0 + kPart * only, cw = min(kPart, n - c0);
     if constexpr (FORM == kGroups) {
-      eliminate_columns<T, RPT, IB, kCap>(x, rows, m, c0, c0, cw, place, piv, rowcol, pcol,
+      eliminate_columns<T, RPT, IB>(x, rows, m, c0, c0, cw, taken, piv, rowcol, pcol,
                                           pive + (c0 - J0), st, stage, cd);
       __syncthreads();
     } else if constexpr (QR > 0) {
