@@ -701,10 +701,12 @@ template <int NT>
 hipError_t launch_fused(fk_mlp* a, const float* x, int rows, float* y) {
   const int pitch = std::max(64 * NT, (a->d_in + 31) / 32 * 32) + 8;
   const size_t lds = sizeof(short) * (size_t)kFusedRows * pitch;
-  // the limit of dynamic LDS is the device's attribute of each kernel
+  // the limit of dynamic LDS belongs to the device and the kernel, not to the
+  // network: always the widest input's, so that no call lowers another's
+  constexpr int kMost = sizeof(short) * kFusedRows * (kFusedMax + 8);
+  static_assert(64 * NT <= kFusedMax && kFusedMax % 32 == 0, "widest layer");
   const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_mlp_bf16<NT>),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize,
-                                           (int)lds);
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, kMost);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_mlp_bf16<NT>, dim3((rows + kFusedRows - 1) / kFusedRows), dim3(256),
                      lds, a->st, x, rows, a->d_in, a->depth, a->d_out, a->p, a->wp, y);

@@ -1,0 +1,46 @@
+"""Calls of the warm-start network beside each other: threads, buffers, memory."""
+import threading
+
+import numpy as np
+import pytest
+
+from oracle import mlp as omlp
+from paper_0711_0999_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+
+def dev(a):
+    import torch
+    return torch.from_numpy(np.ascontiguousarray(a)).cuda()
+
+
+def test_networks_of_two_widths_of_input_in_two_threads(lib):
+    """One kernel serves both networks, with different LDS sizes: no call may
+    take away what the other's launch needs."""
+    print("case: BF16 forward of two networks in two threads", flush=True)
+    nets, xs, want = [], [], []
+    for d_in in (33, 576):
+        shapes = omlp.layer_shapes(d_in, 128, 2, 2)
+        xs.append(dev(inputs.random_rows(70, d_in, seed=d_in + 1)))
+        nets.append(lib.MLP(d_in, 128, 2, 2, params=inputs.network_params(shapes, seed=d_in)))
+        want.append(nets[-1].forward(xs[-1], bf16=True).cpu().numpy())
+    failed = []
+
+    def work(q):
+        try:
+            for _ in range(2000):
+                y = nets[q].forward(xs[q], bf16=True)
+            if not np.array_equal(y.cpu().numpy(), want[q]):
+                failed.append((q, "other values"))
+        except Exception as e:      # a refused launch
+            failed.append((q, e))
+
+    threads = [threading.Thread(target=work, args=(q,)) for q in (0, 1)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    for net in nets:
+        net.close()
+    assert not failed
