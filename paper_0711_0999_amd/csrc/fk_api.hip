@@ -541,11 +541,10 @@ fk_status copy_matrix_out(fk_ctx* c, double* dst, const c64* src, int on_device)
 
 void free_ctx(fk_ctx* c) {
   c64* cs[] = {c->d_w, c->d_sigma, c->d_sigt, c->d_gloc, c->d_gprev,
-               c->d_g0inv, c->d_tmp, c->d_da, c->d_dg, c->d_dz};
+               c->d_g0inv, c->d_tmp, c->d_diff};
   for (c64* p : cs)
     if (p) (void)hipFree(p);
-  double* ds[] = {c->d_cur, c->d_eps, c->d_ebar, c->d_rho, c->d_cos, c->d_sin,
-                  c->d_coef};
+  double* ds[] = {c->d_cur, c->d_eps, c->d_ebar, c->d_rho, c->d_trig, c->d_coef};
   for (double* p : ds)
     if (p) (void)hipFree(p);
   if (c->d_tpos) (void)hipFree(c->d_tpos);
@@ -553,7 +552,6 @@ void free_ctx(fk_ctx* c) {
   for (c64* p : irs)
     if (p) (void)hipFree(p);
   if (c->d_iota) (void)hipFree(c->d_iota);
-  if (c->d_key) (void)hipFree(c->d_key);
   if (c->rep) (void)hipHostFree(c->rep);
   if (c->d_call) (void)hipFree(c->d_call);
   batch_free(c->b64);
@@ -647,14 +645,17 @@ extern "C" fk_status fk_create(const fk_contour* cont, const fk_model* mod,
       gamma[j] = c64{-2.0 * h * h / E, 0.0};
     }
   }
-  std::vector<c64> da(n), dg(n), dz(n);
+  // tables of one kind lie behind each other: one allocation and copy each
+  std::vector<c64> diff(3 * (size_t)n);
+  c64 *da = diff.data(), *dg = da + n, *dz = dg + n;
   da[0] = dg[0] = dz[0] = c64{0.0, 0.0};
   for (int j = 1; j < n; ++j) {
     da[j] = c64{alpha[j].re - alpha[j - 1].re, alpha[j].im - alpha[j - 1].im};
     dg[j] = c64{gamma[j].re - gamma[j - 1].re, gamma[j].im - gamma[j - 1].im};
     dz[j] = c64{zc[j].re - zc[j - 1].re, zc[j].im - zc[j - 1].im};
   }
-  std::vector<double> cs(n_t), sn(n_t);
+  std::vector<double> trig(2 * (size_t)n_t);
+  double *cs = trig.data(), *sn = cs + n_t;
   std::vector<int> tp(n_t);
   for (int i = 0; i < n_t; ++i) {
     const double t = ci.zr[i];
@@ -664,7 +665,9 @@ extern "C" fk_status fk_create(const fk_contour* cont, const fk_model* mod,
   }
   std::vector<c64> w(n);
   for (int j = 0; j < n; ++j) w[j] = c64{ci.wr[j], ci.wi[j]};
-  const double coef[3] = {1.0, 1.0 - mod->w1, mod->w1};
+  // the norms' keys follow the coefficients: cleared by the same copy
+  const double coef[3 + kReportKeys] = {1.0, 1.0 - mod->w1, mod->w1};
+  static_assert(sizeof(unsigned long long) == sizeof(double), "keys");
 
   hipError_t e = hipSuccess;
   if (hip_stream) {
@@ -686,15 +689,11 @@ extern "C" fk_status fk_create(const fk_contour* cont, const fk_model* mod,
   if (e == hipSuccess) e = upload(&c->d_eps, c->eps.data(), sizeof(double) * c->npts);
   if (e == hipSuccess) e = upload(&c->d_ebar, c->ebar.data(), sizeof(double) * c->npts);
   if (e == hipSuccess) e = upload(&c->d_rho, c->rho.data(), sizeof(double) * c->npts);
-  if (e == hipSuccess) e = upload(&c->d_da, da.data(), sizeof(c64) * n);
-  if (e == hipSuccess) e = upload(&c->d_dg, dg.data(), sizeof(c64) * n);
-  if (e == hipSuccess) e = upload(&c->d_dz, dz.data(), sizeof(c64) * n);
-  if (e == hipSuccess) e = upload(&c->d_cos, cs.data(), sizeof(double) * n_t);
-  if (e == hipSuccess) e = upload(&c->d_sin, sn.data(), sizeof(double) * n_t);
+  if (e == hipSuccess) e = upload(&c->d_diff, da, sizeof(c64) * 3 * n);
+  if (e == hipSuccess) e = upload(&c->d_trig, cs, sizeof(double) * 2 * n_t);
   if (e == hipSuccess) e = upload(&c->d_tpos, tp.data(), sizeof(int) * n_t);
   if (e == hipSuccess) e = upload(&c->d_coef, coef, sizeof coef);
-  if (e == hipSuccess) e = hipMalloc(&c->d_key, sizeof(unsigned long long) * kReportKeys);
-  if (e == hipSuccess) e = hipMemset(c->d_key, 0, sizeof(unsigned long long) * kReportKeys);
+  c->d_key = reinterpret_cast<unsigned long long*>(c->d_coef + 3);
   if (e == hipSuccess) e = hipHostMalloc(&c->rep, sizeof(Report), hipHostMallocDefault);
   if (e == hipSuccess) {
     std::vector<int> iota(n);
@@ -715,16 +714,16 @@ extern "C" fk_status fk_create(const fk_contour* cont, const fk_model* mod,
   c->tab.eps = c->d_eps;
   c->tab.ebar = c->d_ebar;
   c->tab.rho = c->d_rho;
-  c->tab.da = c->d_da;
-  c->tab.dg = c->d_dg;
-  c->tab.dz = c->d_dz;
+  c->tab.da = c->d_diff;
+  c->tab.dg = c->d_diff + n;
+  c->tab.dz = c->d_diff + 2 * n;
   c->tab.ca = c64{alpha[0].re - alpha[n - 1].re, alpha[0].im - alpha[n - 1].im};
   c->tab.cg = c64{gamma[0].re - gamma[n - 1].re, gamma[0].im - gamma[n - 1].im};
   c->tab.cz = c64{zc[0].re - zc[n - 1].re, zc[0].im - zc[n - 1].im};
   c->tab.mu = mod->mu;
   c->tab.beta = cont->beta;
-  c->tab.cos_et = c->d_cos;
-  c->tab.sin_et = c->d_sin;
+  c->tab.cos_et = c->d_trig;
+  c->tab.sin_et = c->d_trig + n_t;
   c->tab.t_pos = c->d_tpos;
 
   size_t bb = (size_t)24 << 30;

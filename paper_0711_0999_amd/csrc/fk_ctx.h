@@ -39,13 +39,10 @@ struct fk_ctx {
   double* d_eps = nullptr;
   double* d_ebar = nullptr;
   double* d_rho = nullptr;
-  fk::c64* d_da = nullptr;
-  fk::c64* d_dg = nullptr;
-  fk::c64* d_dz = nullptr;
-  double* d_cos = nullptr;
-  double* d_sin = nullptr;
+  fk::c64* d_diff = nullptr;   // point-to-point differences of alpha, gamma, z
+  double* d_trig = nullptr;    // cos and sin of E t
   int* d_tpos = nullptr;
-  double* d_coef = nullptr;    // {1, 1 - w1, w1}
+  double* d_coef = nullptr;    // {1, 1 - w1, w1}, then the keys
   unsigned long long* d_key = nullptr;   // kReportKeys norms' keys, zero between uses
   fk::Report* rep = nullptr;             // pinned host memory
   char* d_call = nullptr;                // staging of the spectral functions
