@@ -853,8 +853,13 @@ extern "C" fk_status fk_mlp_forward(fk_mlp* a, const float* x_dev, int rows,
   if (!a || !x_dev || !y_dev || rows < 1) return FK_EINVAL;
   // BF16: the fused kernel where a block's activations fit LDS and the waves
   // share the columns evenly (the warm start's network among them: 360,000
-  // rows of 96 -> 512 x 3 -> 2 7.88 -> 0.93 ms); otherwise layer by layer
-  if (bf16 && a->width % 128 == 0 && a->width <= 512 && a->d_in <= kFusedMax &&
+  // rows of 96 -> 512 x 3 -> 2 7.88 -> 0.93 ms); otherwise layer by layer, as
+  // where y overlaps x: a fused block writes its outputs while other blocks
+  // have yet to read their inputs
+  const size_t xa = reinterpret_cast<size_t>(x_dev), ya = reinterpret_cast<size_t>(y_dev);
+  const bool apart = ya >= xa + sizeof(float) * (size_t)rows * a->d_in ||
+                     xa >= ya + sizeof(float) * (size_t)rows * a->d_out;
+  if (bf16 && apart && a->width % 128 == 0 && a->width <= 512 && a->d_in <= kFusedMax &&
       a->d_out <= 16) {
     if (!a->wp) {
       size_t n = 0;

@@ -44,3 +44,21 @@ def test_networks_of_two_widths_of_input_in_two_threads(lib):
     for net in nets:
         net.close()
     assert not failed
+
+
+@pytest.mark.parametrize("at", [0, 1, -1])
+@pytest.mark.parametrize("d_in,d_out", [(96, 2), (16, 16)])
+def test_bf16_outputs_that_overlap_the_inputs(lib, d_in, d_out, at):
+    """y in x's own memory, at its start, its middle and its end: every input is
+    read before any output is written."""
+    print(f"case: BF16 forward into its inputs, {d_in} -> {d_out}, at {at}", flush=True)
+    rows = 40000
+    shapes = omlp.layer_shapes(d_in, 128, 3, d_out)
+    x = dev(inputs.random_rows(rows, d_in, seed=21))
+    net = lib.MLP(d_in, 128, 3, d_out, params=inputs.network_params(shapes, seed=22))
+    want = net.forward(x, bf16=True).cpu().numpy()
+    first = {0: 0, 1: rows * (d_in - d_out) // 2, -1: rows * (d_in - d_out)}[at]
+    y = x.view(-1)[first:first + rows * d_out]
+    net._check(net._lib.fk_mlp_forward(net._h, x.data_ptr(), rows, y.data_ptr(), 1), "forward")
+    assert np.array_equal(y.cpu().numpy().reshape(rows, d_out), want)
+    net.close()
