@@ -608,7 +608,8 @@ struct fk_mlp {
   float* xs = nullptr;   // gathered minibatch
   float* ts = nullptr;
   double* partial = nullptr;   // k_mse's partial sums, then the loss
-  std::vector<float*> parts;   // gradient parts per layer
+  std::vector<float*> parts;   // gradient parts per layer, for up to parts_cap rows
+  int parts_cap = 0;           // (networks that are only evaluated have none)
   short* wp = nullptr;         // weights packed for k_mlp_bf16
   hipStream_t st = nullptr;
   std::string err;
@@ -645,9 +646,6 @@ void free_work(fk_mlp* a) {
   if (a->partial) (void)hipFree(a->partial);
   if (a->xs) (void)hipFree(a->xs);
   if (a->ts) (void)hipFree(a->ts);
-  for (float* q : a->parts)
-    if (q) (void)hipFree(q);
-  a->parts.clear();
   a->xs = a->ts = nullptr;
   a->d0 = a->d1 = nullptr;
   a->partial = nullptr;
@@ -666,13 +664,27 @@ fk_status ensure_work(fk_mlp* a, int rows) {
   MCHK(a, hipMalloc(&a->partial, sizeof(double) * (kMsePartials + 1)));
   MCHK(a, hipMalloc(&a->xs, sizeof(float) * (size_t)rows * a->d_in));
   MCHK(a, hipMalloc(&a->ts, sizeof(float) * (size_t)rows * a->d_out));
+  a->cap = rows;
+  return FK_OK;
+}
+
+void free_parts(fk_mlp* a) {
+  for (float* q : a->parts)
+    if (q) (void)hipFree(q);
+  a->parts.clear();
+  a->parts_cap = 0;
+}
+
+fk_status ensure_parts(fk_mlp* a, int rows) {
+  if (rows <= a->parts_cap) return FK_OK;
+  free_parts(a);
   a->parts.assign(a->depth, nullptr);
   for (int l = 0; l < a->depth; ++l) {
     const int o = a->shapes[l].first, in = a->shapes[l].second;
     MCHK(a, hipMalloc(&a->parts[l], sizeof(float) * ((size_t)o * in + o) *
                                         grad_splits(o, in, rows)));
   }
-  a->cap = rows;
+  a->parts_cap = rows;
   return FK_OK;
 }
 
@@ -729,6 +741,8 @@ hipError_t forward_fused(fk_mlp* a, const float* x, int rows, float* y) {
 // loss and gradient of a batch into a->g; the loss to *loss_dev (device)
 fk_status loss_grad(fk_mlp* a, const float* x, const float* t, int rows,
                     double* loss_dev) {
+  const fk_status s = ensure_parts(a, rows);
+  if (s != FK_OK) return s;
   MCHK(a, forward(a, x, rows, false, nullptr));
   const int L = a->depth;
   const int dout = a->shapes[L - 1].first;
@@ -811,6 +825,7 @@ extern "C" fk_status fk_mlp_destroy(fk_mlp* a) {
   if (!a) return FK_OK;
   if (a->st) (void)hipStreamSynchronize(a->st);
   free_work(a);
+  free_parts(a);
   float* ps[] = {a->p, a->g, a->m, a->v};
   for (float* q : ps)
     if (q) (void)hipFree(q);

@@ -62,3 +62,28 @@ def test_bf16_outputs_that_overlap_the_inputs(lib, d_in, d_out, at):
     net._check(net._lib.fk_mlp_forward(net._h, x.data_ptr(), rows, y.data_ptr(), 1), "forward")
     assert np.array_equal(y.cpu().numpy().reshape(rows, d_out), want)
     net.close()
+
+
+def test_evaluation_allocates_no_gradient_parts(lib):
+    """FP32 rows through 17 layers of 512 x 512: the activations and deltas of
+    2048 rows are 21 buffers of 4 MiB; the gradient's parts would be 17 of 16."""
+    import torch
+    print("case: memory of an FP32 evaluation", flush=True)
+    shapes = omlp.layer_shapes(96, 512, 18, 2)
+    x = dev(inputs.random_rows(2048, 96, seed=31))
+    net = lib.MLP(96, 512, 18, 2, params=inputs.network_params(shapes, seed=32))
+    y = net.forward(x[:1].contiguous())
+    free = torch.cuda.mem_get_info()[0]
+    y = net.forward(x)
+    torch.cuda.synchronize()
+    assert free - torch.cuda.mem_get_info()[0] < 160 * 2 ** 20
+    # the parts come with the first gradient, and again with more rows
+    t = dev(inputs.random_rows(2048, 2, seed=33))
+    for rows in (100, 2048, 700):
+        got = net.loss_grad(x[:rows].contiguous(), t[:rows].contiguous())
+        other = lib.MLP(96, 512, 18, 2, params=net.get_params())
+        want = other.loss_grad(x[:rows].contiguous(), t[:rows].contiguous())
+        other.close()
+        assert got[0] == want[0] and np.array_equal(got[1], want[1])
+    assert np.array_equal(net.forward(x).cpu().numpy(), y.cpu().numpy())
+    net.close()
