@@ -368,15 +368,17 @@ constexpr int kPartLayers = 16;
 struct PartList {
   const float* parts[kPartLayers];
   float* g[kPartLayers];
-  int n[kPartLayers];
+  size_t n[kPartLayers];
   int splits[kPartLayers];
 };
 __global__ void k_sum_parts(PartList pl, const double* __restrict__ partial, int npart,
                             int rows, double* __restrict__ loss) {
-  const int l = blockIdx.y, n = pl.n[l], splits = pl.splits[l];
-  for (int e = blockIdx.x * blockDim.x + threadIdx.x; e < n; e += gridDim.x * blockDim.x) {
+  const int l = blockIdx.y, splits = pl.splits[l];
+  const size_t n = pl.n[l];
+  for (size_t e = blockIdx.x * (size_t)blockDim.x + threadIdx.x; e < n;
+       e += (size_t)gridDim.x * blockDim.x) {
     float s = 0.f;
-    for (int q = 0; q < splits; ++q) s += pl.parts[l][(size_t)q * n + e];
+    for (int q = 0; q < splits; ++q) s += pl.parts[l][q * n + e];
     pl.g[l][e] = s;
   }
   if (loss && l == 0 && blockIdx.x == 0 && threadIdx.x == 0) {
@@ -765,18 +767,18 @@ fk_status loss_grad(fk_mlp* a, const float* x, const float* t, int rows,
   }
   for (int l0 = 0; l0 < L; l0 += kPartLayers) {
     PartList pl{};
-    int most = 0;
+    size_t most = 0;
     const int nl = std::min(kPartLayers, L - l0);
     for (int l = 0; l < nl; ++l) {
       const int o = a->shapes[l0 + l].first, in = a->shapes[l0 + l].second;
       pl.parts[l] = a->parts[l0 + l];
       pl.g[l] = a->g + a->woff[l0 + l];     // W_l and b_l are adjacent
-      pl.n[l] = o * in + o;
+      pl.n[l] = (size_t)o * in + o;
       pl.splits[l] = grad_splits(o, in, rows);
       most = std::max(most, pl.n[l]);
     }
-    hipLaunchKernelGGL(k_sum_parts, dim3((most + 255) / 256, nl), dim3(256), 0, a->st, pl,
-                       a->partial, gb, rows, l0 == 0 ? loss_dev : nullptr);
+    hipLaunchKernelGGL(k_sum_parts, dim3((int)std::min<size_t>((most + 255) / 256, 65536), nl),
+                       dim3(256), 0, a->st, pl, a->partial, gb, rows, l0 == 0 ? loss_dev : nullptr);
     MCHK(a, hipGetLastError());
   }
   return FK_OK;

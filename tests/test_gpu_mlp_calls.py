@@ -87,3 +87,26 @@ def test_evaluation_allocates_no_gradient_parts(lib):
         assert got[0] == want[0] and np.array_equal(got[1], want[1])
     assert np.array_equal(net.forward(x).cpu().numpy(), y.cpu().numpy())
     net.close()
+
+
+def test_gradient_of_a_layer_beyond_two_to_the_31(lib):
+    """65,537 x 32,768 weights in one layer; numbers for which every product and
+    sum is exact."""
+    print("case: gradient of a layer of 2^31 + 32768 weights", flush=True)
+    d_in, width = 32768, 65537
+    x = np.ones((1, d_in), np.float32)
+    x[0, 1::2] = 2.0
+    xd, td = dev(x), dev(np.full((1, 1), -0.5, np.float32))
+    n1 = width * d_in
+    p = np.zeros(n1 + 2 * width + 1, np.float32)   # W1 = b1 = 0: h = 0, y = b2 = 0
+    w2 = (1.0 + np.arange(width) % 5).astype(np.float32)
+    p[n1 + width:n1 + 2 * width] = w2
+    net = lib.MLP(d_in, width, 2, 1, params=p)
+    del p
+    loss, g = net.loss_grad(xd, td)
+    net.close()
+    assert loss == 0.25                            # d = 2 (0 + 0.5) = 1
+    assert np.array_equal(g[n1:n1 + width], w2)
+    assert not g[n1 + width:n1 + 2 * width].any() and g[-1] == 1.0
+    for o in (0, 1, 32768, width - 2, width - 1):
+        assert np.array_equal(g[o * d_in:(o + 1) * d_in], w2[o] * x[0])
