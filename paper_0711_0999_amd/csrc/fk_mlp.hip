@@ -722,8 +722,13 @@ hipError_t launch_fused(fk_mlp* a, const float* x, int rows, float* y) {
   const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_mlp_bf16<NT>),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, kMost);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_mlp_bf16<NT>, dim3((rows + kFusedRows - 1) / kFusedRows), dim3(256),
-                     lds, a->st, x, rows, a->d_in, a->depth, a->d_out, a->p, a->wp, y);
+  constexpr int kMostRows = 1 << 28;   // of a launch: fewer than 2^32 threads
+  for (size_t r0 = 0; r0 < (size_t)rows; r0 += kMostRows) {
+    const int nr = (int)std::min<size_t>(kMostRows, rows - r0);
+    hipLaunchKernelGGL(k_mlp_bf16<NT>, dim3((nr + kFusedRows - 1) / kFusedRows), dim3(256),
+                       lds, a->st, x + r0 * a->d_in, nr, a->d_in, a->depth, a->d_out, a->p,
+                       a->wp, y + r0 * a->d_out);
+  }
   return hipGetLastError();
 }
 // the weights are packed on every call: the parameters may have changed

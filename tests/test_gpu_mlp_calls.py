@@ -110,3 +110,20 @@ def test_gradient_of_a_layer_beyond_two_to_the_31(lib):
     assert not g[n1 + width:n1 + 2 * width].any() and g[-1] == 1.0
     for o in (0, 1, 32768, width - 2, width - 1):
         assert np.array_equal(g[o * d_in:(o + 1) * d_in], w2[o] * x[0])
+
+
+def test_bf16_forward_of_the_most_rows(lib):
+    """2^31 - 1 rows of one input: more threads than one launch can have."""
+    import torch
+    print("case: BF16 forward of 2^31 - 1 rows", flush=True)
+    rows = 2 ** 31 - 1
+    shapes = omlp.layer_shapes(1, 128, 2, 1)
+    net = lib.MLP(1, 128, 2, 1, params=inputs.network_params(shapes, seed=41))
+    x = torch.arange(rows, dtype=torch.int32, device="cuda").remainder_(1009).float()
+    x = x.div_(500.0).view(rows, 1)
+    y = net.forward(x, bf16=True).view(-1)
+    want = net.forward(x[:1009].contiguous(), bf16=True).view(-1)
+    for q in range(0, rows, 1009 * 2 ** 18):
+        part = y[q:q + 1009 * 2 ** 18]
+        assert torch.equal(part, want.repeat(-(-len(part) // 1009))[:len(part)])
+    net.close()
