@@ -275,9 +275,14 @@ __global__ __launch_bounds__(kDosFreq * kDosGroups) void k_wigner_dos(
   const int lq = threadIdx.x % kDosFreq, gr = threadIdx.x / kDosFreq;
   const int q = blockIdx.x * kDosFreq + lq;
   const double om = w[min(q, n_w - 1)];
+  // a phase that overflows counts nothing here, since the window may end before
+  // it (its f_d is then zero); one inside the window makes the result NaN below
   double cj[kDosRun], sj[kDosRun];
 #pragma unroll
-  for (int j = 0; j < kDosRun; ++j) sincos(om * (j * h), &sj[j], &cj[j]);
+  for (int j = 0; j < kDosRun; ++j) {
+    const double ph = om * (j * h);
+    sincos(isinf(ph) ? 0.0 : ph, &sj[j], &cj[j]);
+  }
   for (int r = blockIdx.y; r < n_T; r += gridDim.y) {
     const int i = tix[r];
     const int dmax = min(i, n_t - 1 - i);
@@ -317,6 +322,7 @@ __global__ __launch_bounds__(kDosFreq * kDosGroups) void k_wigner_dos(
       double sum = 0.0;
 #pragma unroll
       for (int p = 0; p < kDosGroups; ++p) sum += part[p][lq];
+      if (isinf(om * (dmax * h))) sum = __builtin_nan("");
       dos[(size_t)r * n_w + q] = -h * sum / 3.14159265358979323846;
     }
   }

@@ -1,0 +1,32 @@
+"""Calls of the DOS at the limits of what it takes: the largest finite
+frequencies, more frequencies than one launch has threads for."""
+import numpy as np
+import pytest
+
+from paper_0711_0999_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+KW = dict(U=1.0, E=1.5, n_eps=2, n_ebar=2, t_min=-0.4, t_max=2.4, dt=0.2, dtau=0.2, beta=1.2)
+
+
+def test_largest_frequencies_at_the_ends_of_the_contour(lib):
+    """Windows of D = 0 and 1 relative times: the phases w d h of later ones
+    overflow, but no result depends on them.  With D = 6 they belong to the
+    window, and the result is no number."""
+    print("case: DOS at the largest finite frequencies", flush=True)
+    big = np.finfo(float).max
+    with lib.Context(**KW) as ctx:
+        ctx.set_sigma(inputs.random_sigma(ctx.n_c, seed=3, scale=0.1))
+        ctx.compute_gloc()
+        g, n_t = ctx.get_gloc(), ctx.n_t
+        for noalloc in (False, True):
+            call = ctx.wigner_dos_noalloc if noalloc else ctx.wigner_dos
+            rho = call([0, n_t - 1, 1], np.array([0.0, big, -big]))
+            assert np.all(np.isfinite(rho))
+            # D = 0: -(h / pi) Im f_0 / 2 at every frequency
+            for r, i in ((0, 0), (1, n_t - 1)):
+                f0 = g[2 * n_t - i, i] - g[i, 2 * n_t - i]
+                assert np.allclose(rho[r], -0.4 / np.pi * 0.5 * f0.imag, rtol=1e-13, atol=0)
+            rho = call([6], np.array([0.0, big, big / 4]))
+            assert np.array_equal(np.isfinite(rho[0]), [True, False, True])
