@@ -269,7 +269,7 @@ __device__ inline c64 retarded_pair(const c64* __restrict__ g, int n_t, int n,
 constexpr int kDosFreq = 32, kDosGroups = 8, kDosRun = 8, kDosStage = 512;
 __global__ __launch_bounds__(kDosFreq * kDosGroups) void k_wigner_dos(
     const c64* __restrict__ g, int n_t, int n, double h, const int* __restrict__ tix,
-    int n_T, const double* __restrict__ w, int n_w, double* __restrict__ dos) {
+    int n_T, const double* __restrict__ w, int n_w, double* __restrict__ dos, size_t ldos) {
   __shared__ c64 f[kDosStage];
   __shared__ double part[kDosGroups][kDosFreq];
   const int lq = threadIdx.x % kDosFreq, gr = threadIdx.x / kDosFreq;
@@ -323,7 +323,7 @@ __global__ __launch_bounds__(kDosFreq * kDosGroups) void k_wigner_dos(
 #pragma unroll
       for (int p = 0; p < kDosGroups; ++p) sum += part[p][lq];
       if (isinf(om * (dmax * h))) sum = __builtin_nan("");
-      dos[(size_t)r * n_w + q] = -h * sum / 3.14159265358979323846;
+      dos[r * ldos + q] = -h * sum / 3.14159265358979323846;
     }
   }
 }
@@ -357,8 +357,14 @@ __global__ void k_moments(const c64* __restrict__ g, int n_t, int n, double h,
 hipError_t launch_wigner_dos(const c64* g, int n_t, int n, double dt, const int* tix,
                              int n_T, const double* w, int n_w, double* dos,
                              hipStream_t st) {
-  hipLaunchKernelGGL(k_wigner_dos, dim3((n_w + kDosFreq - 1) / kDosFreq, n_T < 4096 ? n_T : 4096),
-                     dim3(kDosFreq * kDosGroups), 0, st, g, n_t, n, 2.0 * dt, tix, n_T, w, n_w, dos);
+  constexpr size_t kMost = (size_t)1 << 28;   // frequencies of a launch: below 2^32 threads
+  for (size_t q0 = 0; q0 < (size_t)n_w; q0 += kMost) {
+    const int nq = (int)std::min(kMost, n_w - q0);
+    hipLaunchKernelGGL(k_wigner_dos,
+                       dim3((nq + kDosFreq - 1) / kDosFreq, n_T < 4096 ? n_T : 4096),
+                       dim3(kDosFreq * kDosGroups), 0, st, g, n_t, n, 2.0 * dt, tix, n_T,
+                       w + q0, nq, dos + q0, (size_t)n_w);
+  }
   return hipGetLastError();
 }
 

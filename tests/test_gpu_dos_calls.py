@@ -30,3 +30,20 @@ def test_largest_frequencies_at_the_ends_of_the_contour(lib):
                 assert np.allclose(rho[r], -0.4 / np.pi * 0.5 * f0.imag, rtol=1e-13, atol=0)
             rho = call([6], np.array([0.0, big, big / 4]))
             assert np.array_equal(np.isfinite(rho[0]), [True, False, True])
+
+
+def test_more_frequencies_than_a_launch_has_threads_for(lib):
+    """2^29 + 37 frequencies, eight threads each."""
+    print("case: DOS at 2^29 + 37 frequencies", flush=True)
+    n_w = 2 ** 29 + 37
+    at = np.array([0, 1, 2 ** 28 - 1, 2 ** 28, 2 ** 29 - 1, 2 ** 29, n_w - 1])
+    omega = np.zeros(n_w)
+    omega[at] = 0.25 + np.arange(len(at))
+    with lib.Context(**KW) as ctx:
+        ctx.set_sigma(inputs.random_sigma(ctx.n_c, seed=3, scale=0.1))
+        ctx.compute_gloc()
+        rho = ctx.wigner_dos([5], omega)[0]
+        few = ctx.wigner_dos([5], np.concatenate([omega[at], [0.0]]))[0]
+    assert np.array_equal(rho[at], few[:-1])
+    rho[at] = few[-1]
+    assert np.all(rho == few[-1])
