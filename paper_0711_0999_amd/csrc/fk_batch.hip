@@ -82,6 +82,8 @@ struct fk_batch {
   int* piv = nullptr;
   int* rowcol = nullptr;
   size_t x_cap = 0, b_cap = 0, i_cap = 0, i2_cap = 0;
+  c64* side = nullptr;   // of the chunks and of the impurity slots, in turn
+  size_t side_cap = 0;
   c64* xi = nullptr;
   c64* bi = nullptr;
   std::vector<size_t> imp_s0, imp_i0;   // per active instance: slot offsets
@@ -147,7 +149,7 @@ void drop_graph(fk_batch* b) {
 
 // Point the borrowed storage of a chunk batch at the shared buffers.
 void borrow(fk::Batch<double>& cb, c64* x, size_t xc, c64* bb, size_t bc,
-            int* pv, int* rc, size_t ic) {
+            int* pv, int* rc, size_t ic, c64* side, size_t sc) {
   cb.owns = false;
   cb.x = x;
   cb.x_cap = xc;
@@ -156,6 +158,8 @@ void borrow(fk::Batch<double>& cb, c64* x, size_t xc, c64* bb, size_t bc,
   cb.piv = pv;
   cb.rowcol = rc;
   cb.i_cap = ic;
+  cb.side = side;
+  cb.side_cap = sc;
 }
 
 // Chunk plan for the active instances: point matrices ordered by instance,
@@ -216,7 +220,7 @@ fk_status build_plan(fk_batch* b) {
     group_variant.pop_back();
   }
   // storage needs
-  size_t xmax = 0, bmax = 0, imax = 0;
+  size_t xmax = 0, bmax = 0, imax = 0, smax = 0;
   int status = 0;
   std::vector<std::vector<int>> sizes(groups.size()), sidx(groups.size());
   b->status_inst.clear();
@@ -236,15 +240,22 @@ fk_status build_plan(fk_batch* b) {
     xmax = std::max(xmax, xs);
     bmax = std::max(bmax, bs);
     imax = std::max(imax, is);
+    smax = std::max(smax, side_elems((int)sizes[g].size(),
+                                     *std::max_element(sizes[g].begin(), sizes[g].end())));
   }
+  int nmax = 0;
+  for (int id : b->active) nmax = std::max(nmax, b->inst[id]->ci.n_c);
+  smax = std::max(smax, side_elems((int)b->active.size(), nmax));
   BCHK(b, grow(&b->x, &b->x_cap, xmax));
   BCHK(b, grow(&b->bbuf, &b->b_cap, bmax));
   BCHK(b, grow(&b->piv, &b->i_cap, imax));
   BCHK(b, grow(&b->rowcol, &b->i2_cap, imax));
+  grow_side(&b->side, &b->side_cap, smax);
   b->chunks.resize(groups.size());
   for (size_t g = 0; g < groups.size(); ++g) {
     Chunk& ch = b->chunks[g];
-    borrow(ch.b, b->x, b->x_cap, b->bbuf, b->b_cap, b->piv, b->rowcol, b->i_cap);
+    borrow(ch.b, b->x, b->x_cap, b->bbuf, b->b_cap, b->piv, b->rowcol, b->i_cap, b->side,
+           b->side_cap);
     ch.b.variant = group_variant[g];
     BCHK(b, batch_setup_uneven(ch.b, sizes[g], sidx[g]));
     size_t xo = 0, io = 0;
@@ -276,7 +287,8 @@ fk_status build_plan(fk_batch* b) {
   BCHK(b, grow(&b->pivi, &b->ii_cap, is));
   BCHK(b, grow(&b->rci, &b->ii2_cap, is));
   batch_free(b->impA);
-  borrow(b->impA, b->xi, b->xi_cap, b->bi, b->bi_cap, b->pivi, b->rci, b->ii_cap);
+  borrow(b->impA, b->xi, b->xi_cap, b->bi, b->bi_cap, b->pivi, b->rci, b->ii_cap,
+         b->side, b->side_cap);
   BCHK(b, batch_setup_uneven(b->impA, isz, isx));
   b->n_status = status;
   BCHK(b, grow(&b->d_status, &b->status_cap, (size_t)status));
@@ -461,7 +473,7 @@ extern "C" fk_status fk_batch_destroy(fk_batch* b) {
   drop_graph(b);
   for (Chunk& c : b->chunks) batch_free(c.b);
   batch_free(b->impA);
-  void* ps[] = {b->x, b->bbuf, b->piv, b->rowcol, b->xi, b->bi, b->pivi, b->rci,
+  void* ps[] = {b->x, b->bbuf, b->side, b->piv, b->rowcol, b->xi, b->bi, b->pivi, b->rci,
                 b->d_status, b->d_keys, b->d_inst};
   for (void* p : ps)
     if (p) (void)hipFree(p);

@@ -63,8 +63,8 @@ template <typename T> struct Batch {
   size_t stride = 0;
   cplx<T>* x = nullptr;
   cplx<T>* bbuf = nullptr;     // gathered pivot rows, kBRows x ld per matrix
-  cplx<T>* side = nullptr;     // split panels' pivot rows, kNBO x kNBO per matrix
-  size_t side_cap = 0;         // (batches of at most kSplitMats matrices)
+  cplx<T>* side = nullptr;     // split panels' pivot rows (see side_elems)
+  size_t side_cap = 0;
   int* piv = nullptr;
   int* rowcol = nullptr;
   int* status = nullptr;
@@ -83,7 +83,7 @@ template <typename T> struct Batch {
   size_t nints = 0;
   size_t x_cap = 0, b_cap = 0, i_cap = 0, it_cap = 0;
   int d_cap = 0;
-  bool owns = true;   // false: x/bbuf/piv/rowcol are borrowed shared storage
+  bool owns = true;   // false: x/bbuf/side/piv/rowcol are borrowed shared storage
   int variant = 0;    // trailing-update tile shape (see gje_update)
 };
 
@@ -91,10 +91,10 @@ template <typename T> void batch_free(Batch<T>& b) {
   if (b.owns) {
     if (b.x) (void)hipFree(b.x);
     if (b.bbuf) (void)hipFree(b.bbuf);
+    if (b.side) (void)hipFree(b.side);
     if (b.piv) (void)hipFree(b.piv);
     if (b.rowcol) (void)hipFree(b.rowcol);
   }
-  if (b.side) (void)hipFree(b.side);
   if (b.status) (void)hipFree(b.status);
   if (b.descs) (void)hipFree(b.descs);
   if (b.items) (void)hipFree(b.items);
@@ -198,6 +198,17 @@ template <typename P> hipError_t grow(P** ptr, size_t* cap, size_t want) {
   return e;
 }
 
+// Elements of the side buffer of split panels for nmat matrices of at most nmax
+// rows: kNBO x kNBO each, none where gje_panel does not split.
+inline size_t side_elems(int nmat, int nmax) {
+  return nmat <= kSplitMats && nmax > kSplitRows ? (size_t)kNBO * kNBO * nmat : 0;
+}
+// Such a buffer is a gain in time only: without the memory for it the panels
+// are not split.
+template <typename P> void grow_side(P** ptr, size_t* cap, size_t want) {
+  if (want > 0 && grow(ptr, cap, want) != hipSuccess) (void)hipGetLastError();
+}
+
 // Allocate a uniform batch of cap n x n matrices.  On any failure every buffer
 // is released and the batch is left empty (cap 0, x null), so a caller that
 // checks x and cap reallocates instead of launching on a partial batch.
@@ -222,9 +233,6 @@ hipError_t batch_alloc_parts(Batch<T>& b, int cap, int n, int variant) {
   hipError_t e;
   if ((e = hipMalloc(&b.x, sizeof(cplx<T>) * b.stride * cap)) != hipSuccess) return e;
   if ((e = hipMalloc(&b.bbuf, sizeof(cplx<T>) * (size_t)kBRows * b.ld * cap)) != hipSuccess)
-    return e;
-  if (cap <= kSplitMats &&
-      (e = grow(&b.side, &b.side_cap, (size_t)kNBO * kNBO * cap)) != hipSuccess)
     return e;
   if ((e = hipMalloc(&b.piv, sizeof(int) * (size_t)n * cap)) != hipSuccess) return e;
   if ((e = hipMalloc(&b.rowcol, sizeof(int) * (size_t)n * cap)) != hipSuccess) return e;
@@ -264,13 +272,15 @@ hipError_t batch_alloc_parts(Batch<T>& b, int cap, int n, int variant) {
   if (!it.empty() && (e = hipMemcpy(b.items, it.data(), sizeof(TileItem) * it.size(),
                                     hipMemcpyHostToDevice)) != hipSuccess)
     return e;
+  grow_side(&b.side, &b.side_cap, side_elems(cap, n));   // after what it cannot do without
   b.cap = cap;   // complete: only now does the batch count as allocated
   return hipSuccess;
 }
 
 // Configure the batch for matrices of sizes n[m] (ld = n[m]) packed back to
 // back.  status_idx[m] is the slot of matrix m in the status array passed to
-// batch_invert (the caller zeroes it).  Buffers grow as needed and are kept.
+// batch_invert (the caller zeroes it).  Buffers grow as needed and are kept,
+// but for the side buffer, which the caller lends.
 template <typename T>
 hipError_t batch_setup_uneven(Batch<T>& b, const std::vector<int>& n,
                               const std::vector<int>& status_idx) {
@@ -302,9 +312,6 @@ hipError_t batch_setup_uneven(Batch<T>& b, const std::vector<int>& n,
   hipError_t e;
   if ((e = grow(&b.x, &b.x_cap, xo)) != hipSuccess) return e;
   if ((e = grow(&b.bbuf, &b.b_cap, bo)) != hipSuccess) return e;
-  if (nm <= kSplitMats &&
-      (e = grow(&b.side, &b.side_cap, (size_t)kNBO * kNBO * nm)) != hipSuccess)
-    return e;
   size_t ic = b.i_cap;
   if ((e = grow(&b.piv, &ic, io)) != hipSuccess) return e;
   ic = b.i_cap;
