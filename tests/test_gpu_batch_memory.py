@@ -6,6 +6,8 @@ from paper_0711_0999_amd import inputs
 
 pytestmark = pytest.mark.gpu
 
+torch = pytest.importorskip("torch")   # before the library initializes the device
+
 
 def contour(n_c):
     n_tau = 20 + n_c % 2
@@ -23,7 +25,6 @@ def test_small_chunks_share_their_buffers(lib):
     """16 instances of 256 points, N_c = 200, in 64 chunks of 64 matrices: 147 MB
     of chunk storage and 37 MB of impurity slots, whatever the number of chunks;
     a buffer of 16 MiB of each chunk's own would be another 1074 MB."""
-    import torch
     print("case: memory of 64 chunks", flush=True)
     kw = dict(U=1.0, E=1.5, n_eps=16, n_ebar=16, **contour(200))
     torch.zeros(1, device="cuda")

@@ -201,6 +201,7 @@ def test_judged_loop_accepts_rejects_and_falls_back(lib):
 
 
 @pytest.mark.parametrize("d_in,width,depth,d_out,rows", [
+    # (a block has 64 rows: 127 to 129 lie at the second one's end)
     (96, 512, 4, 2, 127), (96, 512, 4, 2, 129),   # edges of a block of 128 rows
     (33, 128, 2, 16, 300), (64, 256, 3, 1, 128),  # widths of one to three tiles
     (20, 384, 2, 5, 1),

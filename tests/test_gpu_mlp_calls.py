@@ -9,9 +9,10 @@ from paper_0711_0999_amd import inputs
 
 pytestmark = pytest.mark.gpu
 
+torch = pytest.importorskip("torch")   # before the library initializes the device
+
 
 def dev(a):
-    import torch
     return torch.from_numpy(np.ascontiguousarray(a)).cuda()
 
 
@@ -67,7 +68,6 @@ def test_bf16_outputs_that_overlap_the_inputs(lib, d_in, d_out, at):
 def test_evaluation_allocates_no_gradient_parts(lib):
     """FP32 rows through 17 layers of 512 x 512: the activations and deltas of
     2048 rows are 21 buffers of 4 MiB; the gradient's parts would be 17 of 16."""
-    import torch
     print("case: memory of an FP32 evaluation", flush=True)
     shapes = omlp.layer_shapes(96, 512, 18, 2)
     x = dev(inputs.random_rows(2048, 96, seed=31))
@@ -114,7 +114,6 @@ def test_gradient_of_a_layer_beyond_two_to_the_31(lib):
 
 def test_bf16_forward_of_the_most_rows(lib):
     """2^31 - 1 rows of one input: more threads than one launch can have."""
-    import torch
     print("case: BF16 forward of 2^31 - 1 rows", flush=True)
     rows = 2 ** 31 - 1
     shapes = omlp.layer_shapes(1, 128, 2, 1)
@@ -127,3 +126,27 @@ def test_bf16_forward_of_the_most_rows(lib):
         part = y[q:q + 1009 * 2 ** 18]
         assert torch.equal(part, want.repeat(-(-len(part) // 1009))[:len(part)])
     net.close()
+
+
+@pytest.mark.parametrize("d_in,width,depth,d_out,rows", [
+    (96, 512, 4, 2, 1000), (33, 128, 2, 16, 65), (64, 256, 3, 1, 63), (20, 384, 2, 5, 129)])
+def test_fused_evaluation_equals_layer_by_layer(lib, d_in, width, depth, d_out, rows):
+    """With zeros as inputs 577 wide the same network goes layer by layer: the same
+    depths in the same order, bit for bit."""
+    print(f"case: fused and layered BF16, {d_in} -> {width} x {depth - 1} -> {d_out}",
+          flush=True)
+    shapes = omlp.layer_shapes(d_in, width, depth, d_out)
+    p = inputs.network_params(shapes, seed=51)
+    x = inputs.random_rows(rows, d_in, seed=52)
+    w1 = np.zeros((width, 577), np.float32)
+    w1[:, :d_in] = p[:width * d_in].reshape(width, d_in)
+    x2 = np.zeros((rows, 577), np.float32)
+    x2[:, :d_in] = x
+    xd, x2d = dev(x), dev(x2)
+    net = lib.MLP(d_in, width, depth, d_out, params=p)
+    wide = lib.MLP(577, width, depth, d_out,
+                   params=np.concatenate([w1.ravel(), p[width * d_in:]]))
+    y, y2 = net.forward(xd, bf16=True), wide.forward(x2d, bf16=True)
+    assert np.array_equal(y.cpu().numpy(), y2.cpu().numpy())
+    net.close()
+    wide.close()
