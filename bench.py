@@ -39,7 +39,7 @@ PEAK_HBM_GBS = 8000.0
 # scaled by the same counter's reading for a plain 256 MiB copy.  Reported only
 # for that kernel, batch size and schedule (groups of four outer blocks, K up
 # to 512); None until the counters have been taken on the current kernel.
-# Measured: FETCH_SIZE 69358020 KiB x 2.00 + WRITE_SIZE 26671992 KiB x 1.00
+# Measured: FETCH_SIZE 72949560 KiB x 2.00 + WRITE_SIZE 30007057 KiB x 1.00
 # per launch.
 PROFILED_TRAFFIC = {"kernel": "fk::k_update<double, 2>", "batch": 757,
                     "bytes_per_launch": (2.00 * 72949560.0 + 1.00 * 30007057.0) * 1024}

@@ -10,21 +10,24 @@
 //           |re|+|im| among the rows not yet pivoted; groups of kIB columns
 //           are eliminated in registers, and the rest of the quarter, the
 //           other quarter of the half and then the other half receive the
-//           group's (quarter's, half's) transform on the matrix cores.
+//           group's (quarter's, half's) transform on the matrix cores.  For
+//           few matrices the panel is split into launches per quarter or per
+//           group of columns, with its joins between them over all row tiles.
 //   gather  copies the pivot rows of the step into a side buffer B (their
 //           values before the step outside the block, the block's inverse
-//           pivot submatrix inside it); B holds the rows of two blocks.
+//           pivot submatrix inside it); B holds the rows of a group's blocks.
 //   fix     the block's columns of the J0 rows pivoted earlier, from that
 //           inverse (one small product per row tile).  The block now holds
 //           the transformed identity columns M = E[:, P] of all elementary
 //           Gauss-Jordan transforms of the step.
 //   update  every other column tile: C <- mask_P(C) + M B, a batched complex
 //           GEMM on the matrix cores (three real products per complex one),
-//           double-buffered K chunks in LDS, two workgroups per CU.  Blocks
-//           are applied in groups of kGroup (K up to 512, see block_pos): each
-//           block of a group brings the group's earlier blocks' columns up to
-//           date and updates the next block's columns; the last one applies
-//           all the group's transforms to every other column at once.
+//           double-buffered K chunks in LDS, two workgroups per CU (four in
+//           complex64).  Blocks are applied in groups of kGroup (K up to 512,
+//           see block_pos): each block of a group brings the group's earlier
+//           blocks' columns up to date and updates the next block's columns;
+//           the last one applies all the group's transforms to every other
+//           column at once.
 // The host runs the update of the next block's columns first; with the
 // look-ahead schedule it factors that block on a second stream while the big
 // update of the current step runs.
@@ -339,7 +342,7 @@ template <typename T, int IB> struct Candidates {
 // lanes along the rows (IB lanes per row, whole cache lines per access) and
 // transposed through a wave's own part of LDS: one row per lane would touch 64
 // lines per access, and a load or store of a group then costs as much as
-// eliminating it.  pos(i): first list entry of the wave's i-th 64 rows.
+// eliminating it.
 template <typename T, int RPT, int IB>
 __device__ __forceinline__ void load_group(const InMemory<T>& x, int m, int c, int iw,
                                            int tid, cplx<T>* stage, cplx<T> (&v)[RPT][IB]) {

@@ -16,7 +16,7 @@ typedef cplx<float> c32;
 // piv + ioff and rowcol + ioff hold n ints each: piv[c] = row chosen as pivot
 // for column c, rowcol[r] = column whose pivot row is r (-1 while unpivoted).
 // bbuf + boff holds kBRows rows of ld elements: the gathered pivot rows of the
-// one or two outer blocks whose transforms the next update applies.
+// up to kGroup outer blocks whose transforms the group's updates apply.
 struct MatDesc {
   long long xoff;
   long long boff;
@@ -28,7 +28,7 @@ struct MatDesc {
 
 // Tile of an update launch: (matrix, row tile, column tile) and the transform
 // it applies: C <- mask(C) + M B with M the kw columns starting at column
-// jb * kNBO (the transformed identity columns of one or two outer blocks),
+// jb * kNBO (the transformed identity columns of up to kGroup outer blocks),
 // B the rows b0 .. b0 + kw of the side buffer, and the rows whose pivot column
 // lies in [jb kNBO, jb kNBO + kw) masked.  Items of one launch may carry
 // different transforms (uneven batches: each matrix follows its own schedule).
@@ -54,13 +54,14 @@ constexpr int kTile = 64;        // trailing-update tile (rows = cols)
 constexpr int kKC = 16;          // K chunk of the trailing update
 constexpr int kIB = 8;           // panel columns eliminated in registers at once
 constexpr int kPanelThreads = 512;
-constexpr int kGemmThreads = 256;
 // Panels of at most kSplitMats matrices are split into launches while more
 // than kSplitRows rows are left: one matrix of N_c = 1800 14.4 -> 10.7 ms per
 // impurity update, 25 of N_c = 4100 242.6 -> 225.2 ms per step (9.1 and 214
 // with the groups' updates as launches too), 64 complex64 ones of N_c = 600 no
-// change; 225 of N_c = 751 would lose 5%, and a quarter that stays in LDS is
-// too short for ten launches.
+// change.  Above 64 the CUs are busy enough without: split, steps of 80 / 100 /
+// 144 / 196 matrices change by -0.8 / -2.6 / -6.3 / -7.5% at N_c = 1000 (FP64,
+// complex64 alike), by +0.9 / -1.2 / -3.1 / -4.0% at 1800 and by +0.9 / 0 / -1.8
+// / -2.6% at 2300.  A quarter that stays in LDS is too short for ten launches.
 constexpr int kSplitMats = 64;
 constexpr int kSplitRows = 192;
 constexpr int kGroupMats = 32;   // see gje_panel
