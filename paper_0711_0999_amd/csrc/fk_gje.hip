@@ -366,6 +366,8 @@ __device__ __forceinline__ void load_group(const InMemory<T>& x, int m, int c, i
       __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // within the wave
 #pragma unroll
       for (int l = 0; l < IB; ++l) v[i][l] = sw[lane * P + l];
+      // the next rows' writes follow every lane's reads
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     } else {
 #pragma unroll
       for (int l = 0; l < IB; ++l) v[i][l].re = v[i][l].im = T(0);
@@ -392,6 +394,7 @@ __device__ __forceinline__ void store_group(const InMemory<T>& x, int m, int c, 
         const int e = e0 + j * RL + lr;
         if (e < m && lc < iw) *x.at(x.ref(e, c + lc)) = sw[(j * RL + lr) * P + lc];
       }
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     }
   }
 }
