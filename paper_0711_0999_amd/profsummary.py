@@ -8,8 +8,15 @@ kernel and counter, the number of dispatches and the average value.
 Usage: python -m paper_0711_0999_amd.profsummary <results.db> [N]
        python -m paper_0711_0999_amd.profsummary <counter_collection.csv> [N]"""
 import csv
+import re
 import sqlite3
 import sys
+
+
+def _short(name):
+    """A kernel's name without its parameter list; enumeration values among the
+    template arguments, (fk::PanelForm)1, as plain numbers."""
+    return re.sub(r"\((?:\w+::)*\w+\)(?=\d)", "", name).split("(")[0].replace("void ", "")
 
 
 def summarize(db, top=15):
@@ -21,7 +28,7 @@ def summarize(db, top=15):
     out = ["kernel | grid_x (work-items) | calls | total ms | avg ms | % of GPU time",
            "---|---|---|---|---|---"]
     for name, gx, n, tot, avg in rows[:top]:
-        short = name.split("(")[0].replace("void ", "")
+        short = _short(name)
         out.append(f"{short} | {gx} | {n} | {tot / 1e6:.3f} | {avg / 1e6:.4f} | "
                    f"{100.0 * tot / total:.2f}")
     return "\n".join(out)
@@ -51,7 +58,7 @@ def summarize_counters(path, top=15):
                 pass
         acc = {}
         for r in rd:
-            key = (r[ik].split("(")[0].replace("void ", ""),
+            key = (_short(r[ik]),
                    r[ig] if ig is not None else "", r[ic])
             s = acc.setdefault(key, [0, 0.0])
             s[0] += 1

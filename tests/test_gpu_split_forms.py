@@ -63,3 +63,23 @@ def test_33_matrices_against_the_oracle(lib, n_c):
             ctx.compute_gloc(lib.FK_MIXED)
             assert relerr(ctx.get_gloc(), go) < bar
             assert relerr(ctx.get_current()[1], jo) < bar
+
+
+@pytest.mark.parametrize("n_c", [330, 600, 1100, 2200])
+def test_second_stream_and_tile_heights_change_nothing(lib, n_c):
+    """Split panels on the second stream beside the trailing updates, both tile
+    heights: every element takes the same sums."""
+    print(f"case: N_c = {n_c}, look-ahead and tiles of 128 rows", flush=True)
+    with lib.Context(U=1.0, E=1.5, n_eps=2, n_ebar=3, **contour(n_c)) as ctx:
+        ctx.set_sigma(inputs.random_sigma(n_c, seed=n_c, scale=0.1))
+        ctx.set_refinement(0)
+        want = None
+        for rows in (64, 128):
+            for ahead in (0, 1, 1):
+                ctx.set_tuning(tile_rows=rows, batch=6, lookahead=ahead)
+                ctx.compute_gloc()
+                got = [ctx.get_point_green(k) for k in (0, 5)]
+                ctx.compute_gloc(lib.FK_MIXED)
+                got.append(ctx.get_gloc())
+                want = want or got
+                assert all(np.array_equal(a, b) for a, b in zip(got, want)), (rows, ahead)
